@@ -59,7 +59,7 @@ __global__ void prep_kernel(Params P) {
         P.sync->abort = 0;
         Counts c;
         memset(&c, 0, sizeof c);
-        c.active = P.ninst;
+        c.active = P.resume ? 0 : P.ninst;
         P.sync->live = c;
     }
     if (i < 2) {
@@ -84,10 +84,10 @@ __global__ void prep_kernel(Params P) {
         s.r_ub = 0.0;
         s.iters = 0;
         s.status = GD_MAXITER;
-        s.done = 0;
+        s.done = s.tknown = P.resume;
         s.half = 0;
         s.cnt = 0;
-        s.verify = s.replace = s.restart = s.fallback = s.tknown = s.nrep = 0;
+        s.verify = s.replace = s.restart = s.fallback = s.nrep = 0;
         s.start = P.init == GD_INIT_WARM ? GD_INIT_GIVEN : P.init;
         P.st[i] = s;
     }
@@ -180,6 +180,7 @@ const char *last_error() { return g_err.c_str(); }
 void set_error_text(const char *msg) { g_err = msg; }
 
 thread_local gd_launch_info g_last_launch;
+void note_launch(const gd_launch_info &li) { g_last_launch = li; }
 unsigned long long *g_trace = nullptr;
 int64_t g_trace_cap = 0;
 
@@ -294,7 +295,7 @@ int solve_grid(int dtype, int solver, int variant, int blocks_per_cu, const void
     return GD_OK;
 }
 
-int launch_solve(Params &P, const void *k, int64_t blocks_cap, hipStream_t stream) {
+int launch_solve(Params &P, const void *k, int64_t blocks_cap, hipStream_t stream, bool prep = true, bool run = true) {
     DevProps dp;
     int rc = dev_props(&dp);
     if (rc) return rc;
@@ -303,9 +304,13 @@ int launch_solve(Params &P, const void *k, int64_t blocks_cap, hipStream_t strea
     if (P.wait_ticks <= 0) P.wait_ticks = (int64_t)10 * 1000 * dp.wall_khz;  // 10 s
     P.npools = (int32_t)std::min<int64_t>(blocks, NGRP);
     const int prep_blocks = (int)((std::max<int64_t>(P.ninst, NGRP) + 255) / 256);
-    hipLaunchKernelGGL(prep_kernel, dim3(prep_blocks), dim3(256), 0, stream, P);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(GD_EHIP, "prep launch: %s", hipGetErrorString(e));
+    hipError_t e;
+    if (prep) {
+        hipLaunchKernelGGL(prep_kernel, dim3(prep_blocks), dim3(256), 0, stream, P);
+        e = hipGetLastError();
+        if (e != hipSuccess) return fail(GD_EHIP, "prep launch: %s", hipGetErrorString(e));
+    }
+    if (!run) return GD_OK;
     void *args[] = {&P};
     e = hipLaunchKernel(k, dim3((unsigned)blocks), dim3(BLOCK), args, 0, stream);
     if (e != hipSuccess) return fail(GD_EHIP, "solve launch: %s", hipGetErrorString(e));
@@ -424,7 +429,8 @@ std::string key_uniform(int solver, const gd_grid *g, bool aligned) {
 // ---- uniform batches -----------------------------------------------------------
 
 int solve_uniform(int solver, const gd_grid *g, const void *ubar, void *u, const gd_opts *o, void *work,
-                  size_t work_bytes, gd_info *info, void *stream, const TuneCfg *force, const SpecParams *spec) {
+                  size_t work_bytes, gd_info *info, void *stream, const TuneCfg *force, const SpecParams *spec,
+                  UniStage stage, UniView *view) {
     int rc = validate_grid(g);
     if (rc) return rc;
     rc = validate_opts(o);
@@ -443,6 +449,19 @@ int solve_uniform(int solver, const gd_grid *g, const void *ubar, void *u, const
     if (ranges_overlap(ubar, field_bytes, u, field_bytes)) return fail(GD_EINVAL, "ubar and u overlap");
     if (ranges_overlap(ubar, field_bytes, work, need)) return fail(GD_EINVAL, "ubar overlaps the workspace");
     if (ranges_overlap(u, field_bytes, work, need)) return fail(GD_EINVAL, "u overlaps the workspace");
+    if (view) {
+        DevProps dp;
+        if ((rc = dev_props(&dp))) return rc;
+        view->st = (State *)((char *)work + off_st);
+        view->sync = (Sync *)work;
+        view->vec = (char *)work + off_vec;
+        view->vec_bytes = (size_t)nvec_of(solver) * vec_bytes;
+        view->ncu = dp.ncu;
+        view->max_replace = replacements_of(o);
+        view->wait_ticks = wait_ticks_of(o) > 0 ? wait_ticks_of(o) : (int64_t)10 * 1000 * dp.wall_khz;
+        view->traced = g_trace != nullptr;
+        if (stage == UNI_VIEW) return GD_OK;
+    }
     const bool aligned = ((uintptr_t)ubar % 16 == 0) && ((uintptr_t)u % 16 == 0);
     TuneCfg cfg;
     if (force) cfg = *force;
@@ -518,8 +537,12 @@ int solve_uniform(int solver, const gd_grid *g, const void *ubar, void *u, const
     P.wave_claims = cfg.wc;
     P.trace = g_trace;
     P.trace_cap = g_trace_cap;
-    rc = launch_solve(P, kern, blocks_cap, (hipStream_t)stream);
-    if (rc == GD_OK) {
+    P.resume = stage == UNI_PREP_RESUME || stage == UNI_RUN_RESUME;
+    const gd_launch_info before = g_last_launch;
+    rc = launch_solve(P, kern, blocks_cap, (hipStream_t)stream, stage != UNI_RUN_RESUME, stage != UNI_PREP_RESUME);
+    if (stage != UNI_ALL) {  // the class solve is the launch to report
+        g_last_launch = before;
+    } else if (rc == GD_OK) {
         g_last_launch.variant = variant;
         g_last_launch.vw = ts.vw;
         g_last_launch.R = ts.R;

@@ -168,7 +168,7 @@ struct Params {
     int32_t npools;      // tile pools of the launch: min(workgroups, NGRP)
     int32_t wave_claims; // 1: every wave claims its own tiles; 0: a workgroup claims for its waves
     int32_t solver;      // GD_VANCITTERT ... (where a replaced residual is stored)
-    int32_t pad2;
+    int32_t resume;      // spectral solves: 1: a solve on wavenumber classes came first; only the fields it flagged go on
 };
 
 // Launch configuration the autotuner chooses between: target tiles per
@@ -234,8 +234,24 @@ __host__ __device__ constexpr bool mixed_variant_ok(int tsize, int ndim, int vw,
 const void *solve_kernel_ptr(int dtype, int solver, int variant);
 const void *filter_kernel_ptr(int dtype, int variant);
 Geo make_geo(int ndim, int64_t nx, int64_t ny, int64_t nz, int vw, int R, int64_t L, int tail_pct);
+// What solve_uniform does: the whole solve; nothing but lay the workspace out
+// (view); clear the state for a continuation (every field done); run the
+// continuation of the fields that have been flagged since.
+enum UniStage { UNI_ALL, UNI_VIEW, UNI_PREP_RESUME, UNI_RUN_RESUME };
+struct UniView {
+    State *st;
+    Sync *sync;
+    void *vec;         // the solver's vectors: scratch until the solve starts
+    size_t vec_bytes;
+    int ncu;
+    int32_t max_replace;
+    int64_t wait_ticks;
+    bool traced;       // barrier timestamps are being recorded
+};
 int solve_uniform(int solver, const gd_grid *g, const void *ubar, void *u, const gd_opts *o, void *work,
-                  size_t work_bytes, gd_info *info, void *stream, const TuneCfg *force, const SpecParams *spec);
+                  size_t work_bytes, gd_info *info, void *stream, const TuneCfg *force, const SpecParams *spec,
+                  UniStage stage = UNI_ALL, UniView *view = nullptr);
+void note_launch(const gd_launch_info &li);
 int tune_uniform(int solver, const gd_grid *g, const void *ubar, void *u, void *work, size_t wb, gd_info *info,
                  void *stream, gd_tune_info *out, const SpecParams *spec);
 int validate_grid(const gd_grid *g);

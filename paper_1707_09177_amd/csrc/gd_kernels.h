@@ -863,6 +863,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kMinWaves
     constexpr bool TB = var_table(VS);
     uint32_t epoch = 0;
     Snap sn;
+    // a continuation starts at the residual replacement of the fields flagged
+    // for it; their count does not change before every workgroup has arrived
+    // at the first barrier, so all take the same path here
+    const bool resume = var_spec(VS) && P.resume != 0;
+    if (resume && ld_i32(&P.sync->live.active) == 0) return;
+    int act = 0;
+    if (!resume) {
     // reference norm when it is not the initial residual itself (a warm start
     // also needs ||ubar - G ubar||, its acceptance bound)
     if (P.norm_ref == GD_REF_UBAR && P.init != GD_INIT_WARM) {
@@ -876,18 +883,19 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kMinWaves
     if (P.init == GD_INIT_UBAR) run_phase<T, VS, PH_INIT_UBAR>(P, 0, epoch);
     else if (P.init == GD_INIT_ZERO) run_phase<T, VS, PH_INIT_ZERO>(P, 0, epoch);
     else run_phase<T, VS, PH_INIT_GIVEN>(P, 0, epoch);
-    int act = grid_sync<TB>(P, epoch, sn);
+    act = grid_sync<TB>(P, epoch, sn);
     if (act < 0) return;
     // warm starts no better than ubar restart from ubar
     if (sn.fallback > 0) {
         run_phase<T, VS, PH_INIT_UBAR>(P, 0, epoch);
         if ((act = grid_sync<TB>(P, epoch, sn)) < 0) return;
     }
+    }
     // every workgroup sees the same snapshot after each barrier, so all take
     // the same path through the loops
     int it = 0;
-    for (;;) {
-        while (it < P.max_iter && act > 0) {
+    for (bool enter = resume;; enter = false) {
+        while (!enter && it < P.max_iter && act > 0) {
             if constexpr (SOLVER == GD_VANCITTERT) {
                 run_phase<T, VS, PH_VC>(P, it, epoch);
                 if ((act = grid_sync<TB>(P, epoch, sn)) < 0) return;
@@ -912,12 +920,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kMinWaves
             ++it;
             if (sn.verify > 0) break;
         }
-        if (sn.verify == 0) break;
-        // instances whose recursive residual met tol: their true residual
-        // decides; where it is above tol, the residual is replaced by it
-        run_phase<T, VS, PH_VERIFY>(P, it, epoch);
-        if ((act = grid_sync<TB>(P, epoch, sn)) < 0) return;
-        if (sn.replace > 0) {
+        if (!enter) {
+            if (sn.verify == 0) break;
+            // instances whose recursive residual met tol: their true residual
+            // decides; where it is above tol, the residual is replaced by it
+            run_phase<T, VS, PH_VERIFY>(P, it, epoch);
+            if ((act = grid_sync<TB>(P, epoch, sn)) < 0) return;
+        }
+        if (enter || sn.replace > 0) {
             run_phase<T, VS, PH_REPLACE>(P, it, epoch);
             if ((act = grid_sync<TB>(P, epoch, sn)) < 0) return;
         }

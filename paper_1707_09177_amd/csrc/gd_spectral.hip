@@ -33,6 +33,7 @@
 #include <cstring>
 
 #include "gd_internal.h"
+#include "gd_reduced.h"
 #include "gd_twiddle.h"
 
 namespace gdspec {
@@ -849,8 +850,24 @@ int deconvolve_germano(int32_t solver, const gd_grid *g, double gamma, const voi
     }
     const gd_grid v = spectral_grid(g, s);
     const gd::SpecParams sp = spec_params(g, s, ik);
-    rc = gd::solve_uniform(solver, &v, UB, U, o, solve_work, wb - 2 * sb, info, stream, nullptr, &sp);
-    if (rc) return rc;
+    auto general = [&](gd::UniStage stage, gd::UniView *view) {
+        return gd::solve_uniform(solver, &v, UB, U, o, solve_work, wb - 2 * sb, info, stream, nullptr, &sp, stage, view);
+    };
+    gd::UniView view;
+    if ((rc = general(gd::UNI_VIEW, &view))) return rc;
+    const gdred::Fold fold = gdred::fold_of(s.ndim, s.nx, s.ny, s.nz, s.nxs, ik);
+    if (!view.traced && gdred::fits(fold, solver, o->init, s.batch, view.vec_bytes, view.ncu)) {
+        // a tolerance may not be met in the storage type: the general solver
+        // then goes on with the fields concerned (with none it ends at once)
+        const bool resume = o->tol > 0.0;
+        if (resume && (rc = general(gd::UNI_PREP_RESUME, nullptr))) return rc;
+        if ((rc = gdred::solve(solver, g->dtype, fold, s.batch, sp.hw, o, view.max_replace, view.wait_ticks, view.ncu, UB,
+                               U, view.vec, info, view.st, view.sync, resume, st)))
+            return rc;
+        if (resume && (rc = general(gd::UNI_RUN_RESUME, nullptr))) return rc;
+    } else if ((rc = general(gd::UNI_ALL, nullptr))) {
+        return rc;
+    }
     return f32 ? inverse<float>(s, (float *)U, (float *)u, MUL_INV_CN, ik, st)
                : inverse<double>(s, (double *)U, (double *)u, MUL_INV_CN, ik, st);
 }
