@@ -16,21 +16,19 @@
 //
 // A 3D field is a stack of nz planes and a 3D convolution is the sum of three
 // 2D convolutions of the planes shifted by dz = -1, 0, +1, each with its own
-// 3x3 slice of the weights: the 3D matrix-core kernel stages the three
-// planes' tiles in LDS and runs the three 2D products one weight slice at a
-// time into the same registers, then writes bf16 (bias and ReLU, or the ReLU
-// mask) once.
+// 3x3 slice of the weights.
 //
 // Data layout: activations are bfloat16, channels fastest (NHWC, 64 bytes per
 // point).  The four 32 -> 32 layers run as implicit GEMMs on the matrix cores
 // (v_mfma_f32_32x32x16_bf16: 32 points x 32 output channels per wave, K = 9
-// taps x 32 input channels = 18 MFMA steps, FP32 accumulation); the input tile
-// with its periodic halo sits in LDS and the layer's weights in registers.
-// Their input gradients reuse the same kernel with transposed, tap-flipped
-// weights.  The 1 -> 32 and 32 -> 1 layers (288 multiply-adds per point) and
-// the weight gradients of the end layers use plain FP32 arithmetic; the
-// 32 -> 32 weight gradients run on the matrix cores too.  Weight gradients are
-// reduced deterministically (per-block partial sums added in a fixed order).
+// taps x 32 input channels = 18 MFMA steps per slice, FP32 accumulation); the
+// input tile with its periodic halo sits in LDS and the layer's weights in
+// registers.  Their input gradients reuse the same kernels with transposed,
+// tap-flipped weights.  Layer 1 and the input gradient of layer 6 use plain
+// FP32 arithmetic (288 or 864 multiply-adds per point), as do the weight
+// gradients of the end layers; layer 6 and the 32 -> 32 weight gradients run
+// on the matrix cores too.  Weight gradients are reduced deterministically
+// (per-block partial sums added in a fixed order).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -50,6 +48,7 @@ int64_t checked_points(const int64_t *n, int ndim, int64_t cap);
 namespace gdcnn {
 
 typedef __bf16 bf16;
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -58,9 +57,8 @@ constexpr int K9 = 9 * C;       // reduction length of one 3x3 slice
 constexpr int NL = 6;           // layers
 constexpr int K = K9;           // reduction length of a 2D 32 -> 32 layer (one MFMA pass)
 constexpr int NMID = NL - 2;    // 32 -> 32 layers
-constexpr int TY = 8, TX = 32;  // conv tile: 8 rows x 32 points (one MFMA M-tile per row)
-constexpr int PSTR = 40;        // LDS stride of one point (32 channels + 8 pad) in bf16
-constexpr int WGY = 8, WGX = 32;  // weight-gradient tile
+constexpr int TX = 32;          // columns of a conv tile or a weight-gradient strip (one MFMA tile)
+constexpr int PSTR = 40;        // LDS stride of one point in the fused forward's rings (32 channels + 8 pad) in bf16
 constexpr int NW_MID = C * K + C;  // weights + biases of a 32 -> 32 layer
 constexpr int NW_END = K + C;      // either end layer's weights (288) + up to 32 biases
 constexpr int RMS_CHUNKS = 64;
@@ -99,9 +97,16 @@ __device__ __forceinline__ int tap_dx(int t) { return t % 3 - 1; }
 
 // ---------------------------------------------------------------- small kernels
 
-__global__ void k_cvt(const float *p, bf16 *q, int64_t n) {
+// the bf16 weights, and FP32 copies of them for the two end layers (k_conv_end's order)
+__global__ void k_cvt(const float *p, bf16 *q, int64_t n, float *wend, int64_t off_w1, int64_t off_w6, int NT) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) q[i] = (bf16)p[i];
+    if (i < C * NT) {
+        const int c = (int)i / NT, t = (int)i % NT;
+        const int to = ((c >> 3) * (NT / 9) + t / 9) * 72 + (c & 7) * 9 + t % 9;
+        wend[to] = (float)(bf16)p[off_w1 + c * NT + t];
+        wend[C * NT + to] = (float)(bf16)p[off_w6 + t * C + c];
+    }
 }
 
 // Per-dz 3x3 weight slices of the 32 -> 32 layers for the matrix-core kernel,
@@ -129,6 +134,7 @@ __global__ void k_rms_part(const T *ub, int64_t P, double *part) {
     const int b = blockIdx.y, chunk = blockIdx.x;
     const int64_t lo = P * chunk / RMS_CHUNKS, hi = P * (chunk + 1) / RMS_CHUNKS;
     double acc = 0.0;
+#pragma unroll 8
     for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
         const double v = (double)ub[(int64_t)b * P + i];
         acc += v * v;
@@ -151,93 +157,339 @@ __global__ void k_rms_fin(const double *part, int B, int64_t P, double *s) {
     s[b] = r > 0.0 ? r : 1.0;
 }
 
-// layer 1: one input channel (ubar / s, FP32) -> 32 channels, ReLU
-template <typename T, int NT>
-__global__ void k_conv_in(const T *ub, const double *s, const bf16 *w1, const float *b1, bf16 *out, int H, int W,
-                          int nz, int64_t N) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= N) return;
+// One channel -> 32 channels: layer 1 (in = ubar / s, + bias, ReLU) and, with
+// GRAD, the input gradient of layer 6 through the ReLU of layer 5 (in = dL/dz,
+// taps mirrored, masked by a5 > 0).  wt: FP32 copies of the bf16 weights,
+// [channel / 8][dz][channel % 8][tap of the slice].  Bound by the 288 or 864
+// FP32 multiply-adds per point and the 64-byte stores.  A thread takes EPT
+// rows of one column and all channels: the weights are wave-uniform (scalar
+// registers, 72 at a time, each used EPT times) and the window slides along z
+// (3D), a value being loaded once per plane.  The channels of a row of points
+// pass through LDS (wave-private, chunks permuted like the conv tiles) and
+// leave as whole lines.  One point per thread, with the weights converted
+// from bf16 at every use and 16-byte stores 64 bytes apart, took 578 us for
+// 4 x 128^3 (64 us for 8 x 512^2; the input gradient 77 us); this takes
+// 267 us (38 and 62 us).
+constexpr int EPT = 4, EZ = 16;  // rows per thread; planes per run
+// LDS position (in 16-byte chunks) of chunk c of point pix: the four chunks of
+// a point are permuted by its index, so that the 16-byte accesses of 8
+// adjacent points hit 8 different bank groups
+__device__ __forceinline__ int swz(int pix, int c) { return pix * 4 + (c ^ ((pix >> 1) & 3)); }
+template <typename T, int NT, bool GRAD>
+__global__ __launch_bounds__(256) void k_conv_end(const T *in, const double *s, const float *__restrict__ wt,
+                                                  const float *__restrict__ bias, const bf16 *mask, bf16 *out, int H,
+                                                  int W, int nz, int tiles_x, int tiles_y, int zruns) {
+    constexpr int ND = NT / 9;
+    __shared__ uint4 stage[4][EPT][64 * 4];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int blk = blockIdx.x;
+    const int x0 = (blk % tiles_x) * 64, x = min(x0 + lane, W - 1);
+    const int y0 = (blk / tiles_x % tiles_y * 4 + wave) * EPT;
+    const int rest = blk / (tiles_x * tiles_y), zr = rest % zruns;
+    const int64_t smp = rest / zruns;
+    if (y0 >= H) return;  // the whole wave
     const int64_t HW = (int64_t)H * W;
-    const int64_t pz = p / HW;
-    const int rem = (int)(p % HW), y = rem / W, x = rem % W;
-    const float inv = (float)(1.0 / s[pz / nz]);
-    float xv[NT];
+    const int zlo = zr * EZ, zhi = min(nz, zlo + EZ);
+    const float inv = GRAD ? 1.0f : (float)(1.0 / s[smp]);
+    const int xm = wrap(x - 1, W), xp = wrap(x + 1, W);
+    float v[ND][EPT + 2][3];
+    auto load = [&](int z, float (&p)[EPT + 2][3]) {
+        const T *pl = in + (smp * nz + wrap(z, nz)) * HW;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int yy = wrap(y + tap_dy(t), H), xx = wrap(x + tap_dx(t), W);
-        xv[t] = (float)ub[plane_shift(pz, nz, tap_dz<NT>(t)) * HW + (int64_t)yy * W + xx] * inv;
+        for (int r = 0; r < EPT + 2; ++r) {
+            int y = y0 + r - 1;
+            y = y < 0 ? y + H : (y >= H ? (y == H ? 0 : H - 1) : y);  // rows past H feed points that are not stored
+            const T *row = pl + (int64_t)y * W;
+            p[r][0] = (float)row[xm] * inv;
+            p[r][1] = (float)row[x] * inv;
+            p[r][2] = (float)row[xp] * inv;
+        }
+    };
+    if constexpr (ND == 3) {
+        load(zlo - 1, v[1]);
+        load(zlo, v[2]);
     }
-    alignas(16) bf16 o[C];
+    for (int z = zlo; z < zhi; ++z) {
+        if constexpr (ND == 3) {
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-        float acc = b1[c];
+            for (int r = 0; r < EPT + 2; ++r)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) acc += (float)w1[c * NT + t] * xv[t];
-        o[c] = (bf16)fmaxf(acc, 0.0f);
+                for (int k = 0; k < 3; ++k) {
+                    v[0][r][k] = v[1][r][k];
+                    v[1][r][k] = v[2][r][k];
+                }
+            load(z + 1, v[2]);
+        } else {
+            load(z, v[0]);
+        }
+#pragma unroll 1
+        for (int q = 0; q < 4; ++q) {  // 8 channels at a time
+            float acc[EPT][8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float b = GRAD ? 0.0f : bias[8 * q + k];
+#pragma unroll
+                for (int i = 0; i < EPT; ++i) acc[i][k] = b;
+            }
+#pragma unroll
+            for (int d = 0; d < ND; ++d) {
+                const float *w = wt + (q * ND + d) * 72;
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+#pragma unroll
+                    for (int t = 0; t < 9; ++t)
+#pragma unroll
+                        for (int i = 0; i < EPT; ++i)
+                            acc[i][k] += w[k * 9 + t] *
+                                         (GRAD ? v[ND - 1 - d][i + 2 - t / 3][2 - t % 3] : v[d][i + t / 3][t % 3]);
+            }
+#pragma unroll
+            for (int i = 0; i < EPT; ++i) {
+                alignas(16) bf16 o[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) o[k] = (bf16)(GRAD ? acc[i][k] : fmaxf(acc[i][k], 0.0f));
+                stage[wave][i][swz(lane, q)] = *reinterpret_cast<const uint4 *>(o);
+            }
+        }
+        // a wave reads back what it wrote itself: 16 points of 64 bytes per store
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+            if (y0 + i >= H) continue;
+            const int64_t at = ((smp * nz + z) * HW + (int64_t)(y0 + i) * W + x0) * C;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int pt = g * 16 + (lane >> 2);
+                if (x0 + pt >= W) continue;
+                uint4 r = stage[wave][i][swz(pt, lane & 3)];
+                const int64_t to = at + (int64_t)pt * C + (lane & 3) * 8;
+                if constexpr (GRAD) {
+                    alignas(16) bf16 m[8], o[8];
+                    *reinterpret_cast<uint4 *>(m) = *reinterpret_cast<const uint4 *>(mask + to);
+                    *reinterpret_cast<uint4 *>(o) = r;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) o[k] = (float)m[k] > 0.0f ? o[k] : (bf16)0.0f;
+                    r = *reinterpret_cast<const uint4 *>(o);
+                }
+                *reinterpret_cast<uint4 *>(out + to) = r;
+            }
+        }
     }
-    uint4 *dst = reinterpret_cast<uint4 *>(out + p * C);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) dst[q] = reinterpret_cast<const uint4 *>(o)[q];
 }
 
-// 2D 32 -> 32 layer on the matrix cores.  wmat: [cout][K] with
-// K = tap * 32 + cin.  MODE 0 (forward): out = relu(conv(in) + bias);
-// MODE 1 (input gradient): out = conv'(in) * (mask > 0), with `in` the output
-// gradient, `wmat` the transposed weights and `mask` the layer's input
-// activation.
+// 32 -> 32 layers on the matrix cores.  wmat: [dz][cout][K], K = tap * 32 + cin.
+// MODE kFwd: out = relu(conv(in) + bias); kBwd (input gradient): out =
+// conv'(in) * (mask > 0), with `in` the output gradient, the transposed,
+// mirrored weights and `mask` the layer's input activation.
+//
+// A workgroup of four waves owns 4 RB rows x 32 columns of a plane, wave w
+// rows w RB ...  A plane's tile with its halo sits in LDS, written by
+// direct-to-LDS loads (no registers), 64 bytes per point with its chunks
+// permuted (swz).  An input row is read from LDS once (six
+// operands: three taps, two channel halves) and used for the three output
+// rows it belongs to, with the weights in registers.  Products per output run
+// dz, dy, dx, channel half in order.
 constexpr int kFwd = 0, kBwd = 1;
-template <int MODE>
-__global__ __launch_bounds__(256) void k_conv_mid(const bf16 *in, const bf16 *wmat, const float *bias, const bf16 *mask,
-                                                  bf16 *out, int H, int W, int tiles_x, int tiles_y) {
-    __shared__ __attribute__((aligned(16))) bf16 tile[(TY + 2) * (TX + 2) * PSTR];
-    const int blk = blockIdx.x;
-    const int tx = blk % tiles_x, ty = (blk / tiles_x) % tiles_y;
-    const int64_t pz = blk / (tiles_x * tiles_y);  // output plane
-    const int x0 = tx * TX, y0 = ty * TY;
-    const int64_t HW = (int64_t)H * W;
-    const bf16 *inb = in + pz * HW * C;
-    const int tid = threadIdx.x;
-    // tile with a one-point periodic halo, 16-byte chunks of 8 channels
-    for (int q = tid; q < (TY + 2) * (TX + 2) * 4; q += 256) {
-        const int pix = q >> 2, part = q & 3;
-        const int r = pix / (TX + 2), c = pix % (TX + 2);
-        const int gy = (int)((y0 + r - 1 + (int64_t)H) % H), gx = (int)((x0 + c - 1 + (int64_t)W) % W);
-        *reinterpret_cast<uint4 *>(tile + pix * PSTR + part * 8) =
-            *reinterpret_cast<const uint4 *>(inb + ((int64_t)gy * W + gx) * C + part * 8);
+constexpr int TXH = TX + 2;  // tile columns with the halo
+constexpr int RB = 4;        // output rows per wave (8 in 2D measured the same)
+constexpr size_t kConvLds = (size_t)(4 * RB + 2) * TXH * C * sizeof(bf16);  // one plane's tile
+
+// Workgroup barrier ordering LDS only: the threads of the kernels that use
+// it share data through LDS alone, and a full barrier would also wait for the
+// global loads and stores they keep in flight across steps.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// contiguous ranges of the grid per XCD (workgroups are dealt round-robin over
+// the 8 XCDs), so that tiles sharing halos and planes share an L2
+__device__ __forceinline__ int64_t xcd_order() {
+    const int64_t nb = gridDim.x, per = nb / 8, rem = nb % 8, xcd = blockIdx.x % 8, k = blockIdx.x / 8;
+    return xcd * per + (xcd < rem ? xcd : rem) + k;
+}
+
+// start the loads of a plane's tile (rows y0 - 1 .., columns x0 - 1 .., periodic) into LDS
+__device__ __forceinline__ void stage_tile(const bf16 *plane, unsigned char *tile, int x0, int y0, int H, int W,
+                                           int wave, int lane) {
+    constexpr int CH = (4 * RB + 2) * TXH * 4;
+    for (int q0 = wave * 64; q0 < CH; q0 += 256) {
+        const int q = q0 + lane;
+        if (q < CH) {
+            const int pix = q >> 2, c = (q & 3) ^ ((pix >> 1) & 3);
+            const int r = pix / TXH, cc = pix - r * TXH;
+            int gy = y0 + r - 1, gx = x0 + cc - 1;
+            gy = gy < 0 ? gy + H : (gy >= H ? (gy == H ? 0 : H - 1) : gy);  // points past the halo are not used
+            gx = gx < 0 ? gx + W : (gx >= W ? (gx == W ? 0 : W - 1) : gx);
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void *)(plane + ((int64_t)gy * W + gx) * C + c * 8),
+                (__attribute__((address_space(3))) void *)(tile + (size_t)q0 * 16), 16, 0, 0);
+        }
     }
-    const int lane = tid & 63, wave = tid >> 6;
+}
+// wait for this wave's outstanding loads (vmcnt 0), tile loads included
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
+// the products of one 3x3 slice: input rows of `tile` into the wave's RB output rows
+__device__ __forceinline__ void conv_slice(const bf16 *tile, const bf16x8 (&Wf)[K / 16], f32x16 (&acc)[RB], int wave,
+                                           int j, int kh) {
+#pragma unroll
+    for (int ir = 0; ir < RB + 2; ++ir) {
+        bf16x8 A[6];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const int pix = (wave * RB + ir) * TXH + j + (k >> 1);
+            A[k] = *reinterpret_cast<const bf16x8 *>(tile + swz(pix, (k & 1) * 2 + kh) * 8);
+        }
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy) {
+                const int i = ir - dy;
+                if (i >= 0 && i < RB)
+                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Wf[dy * 6 + k], A[k], acc[i], 0, 0, 0);
+            }
+    }
+}
+
+// A lane's outputs: point x, output channels 8 g + 4 kh .. + 3, rows y0 ..
+// y0 + RB - 1 of plane pz.  The half-waves exchange half of their channels
+// (v_permlane32_swap), so that a lane stores 16 channels as two 16-byte pieces
+// (lower half channels 0 - 15, upper half 16 - 31) and not four of 8 bytes.
+template <int MODE>
+__device__ __forceinline__ void conv_store(const f32x16 (&acc)[RB], const f32x16 &bv, const bf16 *mask, bf16 *out,
+                                           int64_t pz, int y0, int x, int H, int W, int kh) {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+        uint32_t p[4][2];  // [g][channel pair]
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                float a = acc[i][4 * g + 2 * k], b = acc[i][4 * g + 2 * k + 1];
+                if constexpr (MODE == kFwd) {
+                    a = fmaxf(a + bv[4 * g + 2 * k], 0.0f);
+                    b = fmaxf(b + bv[4 * g + 2 * k + 1], 0.0f);
+                }
+                const bf16x2 o = {(bf16)a, (bf16)b};
+                p[g][k] = __builtin_bit_cast(uint32_t, o);
+            }
+        alignas(16) uint32_t q[8];
+#pragma unroll
+        for (int g = 0; g < 2; ++g)  // lower half: channels 8 g .. 8 g + 7; upper half: 16 + 8 g ..
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const u32x2 r = __builtin_bit_cast(
+                    u32x2, __builtin_amdgcn_permlane32_swap(p[g][k], p[g + 2][k], false, false));
+                q[4 * g + k] = r[0];
+                q[4 * g + 2 + k] = r[1];
+            }
+        const int y = y0 + i;
+        if (y >= H || x >= W) continue;
+        const int64_t idx = ((pz * H + y) * (int64_t)W + x) * C + 16 * kh;
+        if constexpr (MODE == kBwd) {
+            alignas(16) bf16 m[16];
+            bf16 *o = reinterpret_cast<bf16 *>(q);
+            *reinterpret_cast<uint4 *>(m) = *reinterpret_cast<const uint4 *>(mask + idx);
+            *reinterpret_cast<uint4 *>(m + 8) = *reinterpret_cast<const uint4 *>(mask + idx + 8);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) o[k] = (float)m[k] > 0.0f ? o[k] : (bf16)0.0f;
+        }
+        *reinterpret_cast<uint4 *>(out + idx) = *reinterpret_cast<const uint4 *>(q);
+        *reinterpret_cast<uint4 *>(out + idx + 8) = *reinterpret_cast<const uint4 *>(q + 4);
+    }
+}
+
+template <int MODE>
+__device__ __forceinline__ f32x16 conv_bias(const float *bias, int kh) {
+    f32x16 bv = {};
+    if constexpr (MODE == kFwd)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) bv[v] = bias[8 * (v >> 2) + 4 * kh + (v & 3)];
+    return bv;
+}
+
+// 2D.  Bound by HBM: one read and one write of 64 bytes per point, the input
+// gradient two reads.  Two or more workgroups per CU: one loads its tile
+// while another computes.  A tile of eight rows with every operand read from
+// LDS for each output row and 2-byte stores took 131 (input gradient 311) us
+// for 8 x 512^2; this takes 72 (91) us.
+template <int MODE>
+__global__ __launch_bounds__(256, 3) void k_conv_mid(const bf16 *in, const bf16 *wmat, const float *bias,
+                                                     const bf16 *mask, bf16 *out, int H, int W, int tiles_x,
+                                                     int tiles_y) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char conv_tile[];
+    const int64_t blk = xcd_order();
+    const int x0 = (int)(blk % tiles_x) * TX, y0 = (int)(blk / tiles_x % tiles_y) * 4 * RB;
+    const int64_t pz = blk / ((int64_t)tiles_x * tiles_y);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int j = lane & 31, kh = lane >> 5;
-    bf16x8 Bf[K / 16];
+    stage_tile(in + pz * H * W * C, conv_tile, x0, y0, H, W, wave, lane);
+    bf16x8 Wf[K / 16];
 #pragma unroll
-    for (int ks = 0; ks < K / 16; ++ks) Bf[ks] = *reinterpret_cast<const bf16x8 *>(wmat + j * K + ks * 16 + kh * 8);
-    float bj = 0.0f;
-    if constexpr (MODE == kFwd) bj = bias[j];
+    for (int ks = 0; ks < K / 16; ++ks) Wf[ks] = *reinterpret_cast<const bf16x8 *>(wmat + j * K + ks * 16 + kh * 8);
+    f32x16 acc[RB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i) acc[i] = f32x16{};
+    wait_loads();
     __syncthreads();
-    for (int rr = wave; rr < TY; rr += 4) {
-        f32x16 acc = {};
-        bf16x8 Af[K / 16];  // every operand load issued before the first product
+    conv_slice(reinterpret_cast<const bf16 *>(conv_tile), Wf, acc, wave, j, kh);
+    conv_store<MODE>(acc, conv_bias<MODE>(bias, kh), mask, out, pz, y0 + wave * RB, x0 + j, H, W, kh);
+}
+
+// 3D: a workgroup marches along z through a run of planes.  Four plane tiles
+// sit in LDS (157 KB: one workgroup per CU, one wave per SIMD): the three an
+// output plane needs and the next one, in flight while the products run, so an
+// activation is loaded once per run and not once per plane that needs it.
+// With a whole SIMD's registers a wave keeps the weights of all 27 taps (216
+// registers) for the whole run.  Bound by the matrix cores (216 products of
+// 32 clocks per wave and plane, against 1700 clocks of LDS reads per CU).
+// All three planes' tiles in LDS per output plane, the weights loaded per
+// plane and every operand read from LDS for each output row took 1387 us for
+// 4 x 128^3; this takes 507 us.
+template <int MODE>
+__global__ __launch_bounds__(256, 1) void k_conv_mid3(const bf16 *in, const bf16 *slices, const float *bias,
+                                                      const bf16 *mask, bf16 *out, int H, int W, int nz, int tiles_x,
+                                                      int tiles_y, int zruns, int zrun) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char conv_tile[];
+    const int64_t blk = xcd_order();
+    const int x0 = (int)(blk % tiles_x) * TX, y0 = (int)(blk / tiles_x % tiles_y) * 4 * RB;
+    const int64_t rest = blk / ((int64_t)tiles_x * tiles_y);
+    const int zlo = (int)(rest % zruns) * zrun, zhi = min(nz, zlo + zrun);
+    const int64_t p0 = rest / zruns * nz;  // the sample's first plane
+    const int64_t HW = (int64_t)H * W;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int j = lane & 31, kh = lane >> 5;
+    constexpr size_t TB = kConvLds;
+    // plane z (periodic) into ring slot (z - zlo + 1) mod 4
+    auto stage = [&](int z) {
+        stage_tile(in + (p0 + wrap(z, nz)) * HW * C, conv_tile + (size_t)((z - zlo + 1) & 3) * TB, x0, y0, H, W,
+                        wave, lane);
+    };
+    stage(zlo - 1);
+    stage(zlo);
+    stage(zlo + 1);
+    bf16x8 Wf[3][K / 16];
 #pragma unroll
-        for (int ks = 0; ks < K / 16; ++ks) {
-            const int t = ks >> 1, dy = t / 3, dx = t % 3;
-            const int pix = (rr + dy) * (TX + 2) + (j + dx);
-            Af[ks] = *reinterpret_cast<const bf16x8 *>(tile + pix * PSTR + (ks & 1) * 16 + kh * 8);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+    for (int d = 0; d < 3; ++d)
 #pragma unroll
-        for (int ks = 0; ks < K / 16; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Af[ks], Bf[ks], acc, 0, 0, 0);
-        const int y = y0 + rr;
-        if (y >= H) continue;
+        for (int ks = 0; ks < K / 16; ++ks)
+            Wf[d][ks] = *reinterpret_cast<const bf16x8 *>(slices + (size_t)d * C * K9 + j * K + ks * 16 + kh * 8);
+    const f32x16 bv = conv_bias<MODE>(bias, kh);
+    wait_loads();
+    for (int z = zlo; z < zhi; ++z) {
+        lds_barrier();  // every wave's share of plane z + 1 is in LDS, and plane z - 2 has been read by all
+        if (z + 2 <= zhi) stage(z + 2);
+        f32x16 acc[RB];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int i = 8 * (v >> 2) + 4 * kh + (v & 3);
-            const int x = x0 + i;
-            if (x >= W) continue;
-            const int64_t idx = ((pz * H + y) * (int64_t)W + x) * C + j;
-            float val = acc[v];
-            if constexpr (MODE == kBwd) val = (float)mask[idx] > 0.0f ? val : 0.0f;
-            else val = fmaxf(val + bj, 0.0f);
-            out[idx] = (bf16)val;
-        }
+        for (int i = 0; i < RB; ++i) acc[i] = f32x16{};
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+            conv_slice(reinterpret_cast<const bf16 *>(conv_tile + (size_t)((z - zlo + d) & 3) * TB), Wf[d], acc,
+                            wave, j, kh);
+        wait_loads();  // plane z + 2, before the stores: they need not be waited for
+        conv_store<MODE>(acc, bv, mask, out, p0 + z, y0 + wave * RB, x0 + j, H, W, kh);
     }
 }
 
@@ -268,21 +520,11 @@ constexpr int UBATCH = 16;    // ubar rows loaded together, every UBATCH steps
 constexpr size_t kRingBytes = (size_t)(NL - 1) * (RSL + 1) * FRC * PSTR * sizeof(bf16);
 constexpr size_t kFusedLds = kRingBytes + URS * URC * sizeof(float) + 2 * 8 * 64 * sizeof(float);
 static_assert(kFusedLds <= 160 * 1024, "LDS of one CU");
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // max(x, 0) as one integer max on the bits (a negative float is a negative
 // integer): fmaxf also quiets signalling NaNs, one more instruction per value
 __device__ __forceinline__ float relu_bits(float x) {
     return __builtin_bit_cast(float, max(__builtin_bit_cast(int, x), 0));
-}
-
-// Workgroup barrier ordering LDS only: the fused kernel's threads share data
-// through LDS alone, and a full barrier would also wait for the global loads
-// it keeps in flight across steps.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 template <typename T>
@@ -458,104 +700,106 @@ __global__ __launch_bounds__(FTHREADS) void k_fwd2d_fused(const T *ub, const dou
     zsum_out(nstep - 1);
 }
 
-// A whole 3D 32 -> 32 layer in one pass: the input tiles of planes z - 1, z,
-// z + 1 (each with its periodic x-y halo) sit in LDS, and every output row
-// accumulates its 3 x 18 MFMA steps in registers, one weight slice at a time
-// (slices: [dz][cout][K], K = tap * 32 + cin), so no FP32 partial buffer goes
-// through HBM.  MODE kFwd: out = relu(conv(in) + bias); kBwd: out =
-// conv'(in) * (mask > 0) with the transposed, mirrored slices.
-constexpr size_t kMid3Lds = (size_t)3 * (TY + 2) * (TX + 2) * PSTR * sizeof(bf16);
-template <int MODE>
-__global__ __launch_bounds__(256) void k_conv_mid3(const bf16 *in, const bf16 *slices, const float *bias,
-                                                   const bf16 *mask, bf16 *out, int H, int W, int nz, int tiles_x,
-                                                   int tiles_y) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char mid3_lds[];
-    bf16 *tiles = reinterpret_cast<bf16 *>(mid3_lds);
-    constexpr int TP = (TY + 2) * (TX + 2) * PSTR;  // one plane's tile
-    const int blk = blockIdx.x;
-    const int tx = blk % tiles_x, ty = (blk / tiles_x) % tiles_y;
-    const int64_t pz = blk / (tiles_x * tiles_y);  // output plane
-    const int x0 = tx * TX, y0 = ty * TY;
-    const int64_t HW = (int64_t)H * W;
-    const int tid = threadIdx.x;
-    for (int dzi = 0; dzi < 3; ++dzi) {
-        const bf16 *inb = in + plane_shift(pz, nz, dzi - 1) * HW * C;
-        for (int q = tid; q < (TY + 2) * (TX + 2) * 4; q += 256) {
-            const int pix = q >> 2, part = q & 3;
-            const int r = pix / (TX + 2), c = pix % (TX + 2);
-            const int gy = (int)((y0 + r - 1 + (int64_t)H) % H), gx = (int)((x0 + c - 1 + (int64_t)W) % W);
-            *reinterpret_cast<uint4 *>(tiles + dzi * TP + pix * PSTR + part * 8) =
-                *reinterpret_cast<const uint4 *>(inb + ((int64_t)gy * W + gx) * C + part * 8);
-        }
-    }
-    const int lane = tid & 63, wave = tid >> 6;
-    const int j = lane & 31, kh = lane >> 5;
-    constexpr int RPW = TY / 4;  // output rows per wave
-    f32x16 acc[RPW];
-#pragma unroll
-    for (int i = 0; i < RPW; ++i) acc[i] = f32x16{};
-    __syncthreads();
-    for (int dzi = 0; dzi < 3; ++dzi) {
-        bf16x8 Bf[K / 16];
-        const bf16 *wm = slices + (size_t)dzi * C * K9;
-#pragma unroll
-        for (int ks = 0; ks < K / 16; ++ks) Bf[ks] = *reinterpret_cast<const bf16x8 *>(wm + j * K + ks * 16 + kh * 8);
-        const bf16 *tl = tiles + dzi * TP;
-#pragma unroll
-        for (int i = 0; i < RPW; ++i) {
-            const int rr = wave + 4 * i;
-            bf16x8 Af[K / 16];  // every operand load issued before the first product
-#pragma unroll
-            for (int ks = 0; ks < K / 16; ++ks) {
-                const int t = ks >> 1, dy = t / 3, dx = t % 3;
-                const int pix = (rr + dy) * (TX + 2) + (j + dx);
-                Af[ks] = *reinterpret_cast<const bf16x8 *>(tl + pix * PSTR + (ks & 1) * 16 + kh * 8);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int ks = 0; ks < K / 16; ++ks) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Af[ks], Bf[ks], acc[i], 0, 0, 0);
-        }
-    }
-    float bj = 0.0f;
-    if constexpr (MODE == kFwd) bj = bias[j];
-#pragma unroll
-    for (int i = 0; i < RPW; ++i) {
-        const int y = y0 + wave + 4 * i;
-        if (y >= H) continue;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int xi = 8 * (v >> 2) + 4 * kh + (v & 3);
-            const int x = x0 + xi;
-            if (x >= W) continue;
-            const int64_t idx = ((pz * H + y) * (int64_t)W + x) * C + j;
-            float val = acc[i][v];
-            if constexpr (MODE == kBwd) val = (float)mask[idx] > 0.0f ? val : 0.0f;
-            else val = fmaxf(val + bj, 0.0f);
-            out[idx] = (bf16)val;
-        }
-    }
-}
-
-// layer 6: 32 channels -> 1, no activation: z
+// layer 6: 32 channels -> 1, no activation: z.  On the matrix cores: one
+// product pair gives, for 32 points, the contributions D[tap][point] =
+// sum_c a[point][c] w6[tap][c] of all 9 or 27 taps; they go to LDS, and z at a
+// point is the sum over the taps of D[tap][point + off(tap)].  A workgroup
+// owns 16 x 32 points of a run of OZ planes (3D; one plane in 2D) and marches
+// along z, keeping the sums of the planes that still miss a neighbour in
+// registers, so an activation is read once and not once per tap.
+// Bound by that read: reading 64 bytes per tap and point took 1191 us for
+// 4 x 128^3 (113 us for 8 x 512^2); this takes 137 (29) us.
+constexpr int OY = 16, OX = 32, OZ = 16;
+constexpr int OPTS = (OY + 2) * (OX + 2), OGRP = (OPTS + 31) / 32;  // tile points with the halo, groups of 32
+constexpr int OST = OGRP * 32;                                      // LDS row of one tap
 template <int NT>
-__global__ void k_conv_out(const bf16 *a, const bf16 *w6, const float *b6, float *z, int H, int W, int nz, int64_t N) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= N) return;
-    const int64_t HW = (int64_t)H * W;
-    const int64_t pz = p / HW;
-    const int rem = (int)(p % HW), y = rem / W, x = rem % W;
-    float acc = b6[0];
-    for (int t = 0; t < NT; ++t) {
-        const int yy = wrap(y + tap_dy(t), H), xx = wrap(x + tap_dx(t), W);
-        const uint4 *src =
-            reinterpret_cast<const uint4 *>(a + (plane_shift(pz, nz, tap_dz<NT>(t)) * HW + (int64_t)yy * W + xx) * C);
-        alignas(16) bf16 v[C];
+__global__ __launch_bounds__(256) void k_conv_out(const bf16 *a, const bf16 *w6, const float *b6, float *z, int H,
+                                                  int W, int nz, int tiles_x, int tiles_y, int zruns) {
+    constexpr int ND = NT / 9;
+    constexpr int GPW = (OGRP + 3) / 4;  // groups per wave
+    __shared__ float D[NT * OST];
+    const int64_t blk = xcd_order();
+    const int x0 = (int)(blk % tiles_x) * OX, y0 = (int)(blk / tiles_x % tiles_y) * OY;
+    const int64_t rest = blk / ((int64_t)tiles_x * tiles_y);
+    const int zr = (int)(rest % zruns);
+    const int64_t smp = rest / zruns, HW = (int64_t)H * W;
+    // 2D: every plane is a sample of its own (nz = 1)
+    const int zlo = zr * OZ, zhi = min(nz, zlo + OZ);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int j = lane & 31, kh = lane >> 5;
+    // weights: row = tap (rows past NT are zero), k = channel
+    bf16x8 Wf[2];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) reinterpret_cast<uint4 *>(v)[q] = src[q];
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int c = 0; c < C; ++c) acc += (float)v[c] * (float)w6[t * C + c];
+        for (int e = 0; e < 8; ++e) Wf[h][e] = j < NT ? w6[min(j, NT - 1) * C + h * 16 + kh * 8 + e] : (bf16)0.0f;
+    // this lane's point of each of its wave's groups, as an offset in a plane
+    int64_t poff[GPW];
+#pragma unroll
+    for (int g = 0; g < GPW; ++g) {
+        const int pix = min((wave + 4 * g) * 32 + j, OPTS - 1);
+        const int r = pix / (OX + 2), c = pix - r * (OX + 2);
+        int gy = y0 + r - 1, gx = x0 + c - 1;
+        gy = gy < 0 ? gy + H : (gy >= H ? (gy == H ? 0 : H - 1) : gy);
+        gx = gx < 0 ? gx + W : (gx >= W ? (gx == W ? 0 : W - 1) : gx);
+        poff[g] = ((int64_t)gy * W + gx) * C + kh * 8;
     }
-    z[p] = acc;
+    bf16x8 A[GPW][2];
+    auto load = [&](int q) {  // plane q of the sample, periodic
+        const bf16 *pl = a + (smp * nz + wrap(q, nz)) * HW * C;
+#pragma unroll
+        for (int g = 0; g < GPW; ++g)
+            if (wave + 4 * g < OGRP) {
+                A[g][0] = *reinterpret_cast<const bf16x8 *>(pl + poff[g]);
+                A[g][1] = *reinterpret_cast<const bf16x8 *>(pl + poff[g] + 16);
+            }
+    };
+    constexpr int PP = OY * OX / 256;  // output points per thread
+    float prev[PP], cur[PP];           // sums of output planes q - 1 and q
+#pragma unroll
+    for (int i = 0; i < PP; ++i) prev[i] = cur[i] = 0.0f;
+    const float b = b6[0];
+    const int q0 = ND == 1 ? zlo : zlo - 1, q1 = ND == 1 ? zhi : zhi + 1;
+    load(q0);
+    for (int q = q0; q < q1; ++q) {
+#pragma unroll
+        for (int g = 0; g < GPW; ++g) {
+            if (wave + 4 * g >= OGRP) continue;
+            f32x16 d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Wf[0], A[g][0], f32x16{}, 0, 0, 0);
+            d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Wf[1], A[g][1], d, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int t = 8 * (v >> 2) + 4 * kh + (v & 3);
+                if (8 * (v >> 2) < NT && t < NT) D[t * OST + (wave + 4 * g) * 32 + j] = d[v];
+            }
+        }
+        if (q + 1 < q1) load(q + 1);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < PP; ++i) {
+            const int pt = tid + 256 * i, py = pt / OX, px = pt % OX;
+            float sd[ND];
+#pragma unroll
+            for (int d = 0; d < ND; ++d) {
+                sd[d] = 0.0f;
+#pragma unroll
+                for (int t = 0; t < 9; ++t)
+                    sd[d] += D[(d * 9 + t) * OST + (py + t / 3) * (OX + 2) + px + t % 3];
+            }
+            const int y = y0 + py, x = x0 + px;
+            const bool ok = y < H && x < W;
+            if constexpr (ND == 1) {
+                if (ok) z[(smp * nz + q) * HW + (int64_t)y * W + x] = sd[0] + b;
+            } else {
+                // dz = +1 taps of plane q complete output plane q - 1; dz = -1 taps open plane q + 1
+                if (ok && q - 1 >= zlo && q - 1 < zhi)
+                    z[(smp * nz + q - 1) * HW + (int64_t)y * W + x] = prev[i] + sd[2] + b;
+                prev[i] = cur[i] + sd[1];
+                cur[i] = sd[0];
+            }
+        }
+        __syncthreads();
+    }
 }
 
 // out = G in: the periodic trapezoidal filter (1/4, 1/2, 1/4) per axis (the
@@ -634,186 +878,260 @@ __global__ void k_loss_fin(const double *part, int64_t nblk, int64_t N, double *
     if (threadIdx.x == 0) loss[0] = red[0] / (double)N;
 }
 
-// input gradient of layer 6 through the ReLU of layer 5:
-// dz5[p][c] = (sum_t W6[t][c] dy[p - off(t)]) * (a5[p][c] > 0)
-template <int NT>
-__global__ void k_out_bwd(const float *dy, const bf16 *w6, const bf16 *a5, bf16 *dz, int H, int W, int nz, int64_t N) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= N) return;
-    const int64_t HW = (int64_t)H * W;
-    const int64_t pz = p / HW;
-    const int rem = (int)(p % HW), y = rem / W, x = rem % W;
-    float g[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int yy = wrap(y - tap_dy(t), H), xx = wrap(x - tap_dx(t), W);
-        g[t] = dy[plane_shift(pz, nz, -tap_dz<NT>(t)) * HW + (int64_t)yy * W + xx];
-    }
-    alignas(16) bf16 m[C], o[C];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) reinterpret_cast<uint4 *>(m)[q] = reinterpret_cast<const uint4 *>(a5 + p * C)[q];
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-        float acc = 0.0f;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) acc += (float)w6[t * C + c] * g[t];
-        o[c] = (bf16)((float)m[c] > 0.0f ? acc : 0.0f);
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) reinterpret_cast<uint4 *>(dz + p * C)[q] = reinterpret_cast<const uint4 *>(o)[q];
+// ------------------------------------------------------- weight gradients
+// A unit of work is one strip of columns of one plane, `ru` rows; a wave
+// marches down its units and keeps the sums in registers; a workgroup adds
+// its four waves' sums in wave order.
+
+// plane, first column and rows of unit n
+struct Unit {
+    int64_t b;
+    int x0, ya, yb;
+};
+__device__ __forceinline__ Unit unit_of(int64_t n, int strip, int tiles_x, int chunks, int ru, int H) {
+    Unit u;
+    u.x0 = (int)(n % tiles_x) * strip;
+    u.ya = (int)(n / tiles_x % chunks) * ru;
+    u.yb = min(H, u.ya + ru);
+    u.b = n / ((int64_t)tiles_x * chunks);
+    return u;
 }
 
-// Weight gradient of one layer (one 3x3 slice: the input x is read from the
-// plane shifted by dzo) over the points of this block's tiles:
-// dW[o][t][c] = sum_p g[p][o] x[p + off(t)][c], db[o] = sum_p g[p][o].
-// x: CI channels (32: bf16 activations; 1: ubar / s); g: CO channels
-// (32: bf16 gradients; 1: FP32 dL/dy).  part[block][CO*9*CI + CO].
-template <int CI, int CO, typename T>
-__global__ __launch_bounds__(256) void k_wgrad(const bf16 *xa, const T *ub, const double *s, const bf16 *ga,
-                                               const float *gf, float *part, int H, int W, int nz, int dzo,
-                                               int tiles_x, int tiles_y, int64_t ntiles) {
-    constexpr int NWL = CO * 9 * CI + CO;
-    constexpr int SLOTS = (NWL + 255) / 256;
-    __shared__ float xs[(WGY + 2) * (WGX + 2) * CI];
-    __shared__ float gs[WGY * WGX * CO];
-    const int tid = threadIdx.x;
-    float acc[SLOTS];
-#pragma unroll
-    for (int k = 0; k < SLOTS; ++k) acc[k] = 0.0f;
+// End layers, one 3x3 slice: 32 channels v (bf16) against one FP32 channel f,
+//   OUT = false (layer 1):  dW[o][t] = sum_p v[p][o] f[p + off(t)],  v = dz, f = ubar / s
+//   OUT = true  (layer 6):  dW[t][c] = sum_q v[q][c] f[q - off(t)],  v = a5, f = dL/dz
+// and the bias gradient.  Four lanes hold a point's 32 channels (one 16-byte
+// load each), 16 points per wave; f's 3x3 window slides down the march, three
+// new values per row.  FP32 throughout.  Bound by reading v once (64 bytes
+// per point): one thread per weight over an LDS tile took 422 and 502 us for
+// 8 x 512^2; this takes 63 and 50 us.
+constexpr int ENS = 16;  // columns per unit
+template <typename T, bool OUT>
+__global__ __launch_bounds__(256) void k_wgrad_end(const bf16 *va, const T *f, const double *s, float *part, int H,
+                                                   int W, int nz, int dzo, int tiles_x, int chunks, int ru,
+                                                   int64_t nunits) {
+    constexpr int NWL = OUT ? K9 + 1 : K9 + C;
+    __shared__ float red[NWL];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ch = lane & 3;
     const int64_t HW = (int64_t)H * W;
-    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const int tx = (int)(tile % tiles_x), ty = (int)((tile / tiles_x) % tiles_y);
-        const int64_t b = tile / ((int64_t)tiles_x * tiles_y);  // output plane
-        const int64_t bx = plane_shift(b, nz, dzo);              // input plane
-        const int x0 = tx * WGX, y0 = ty * WGY;
-        for (int q = tid; q < (WGY + 2) * (WGX + 2) * CI; q += 256) {
-            const int pix = q / CI, c = q % CI;
-            const int r = pix / (WGX + 2), cc = pix % (WGX + 2);
-            const int gy = (int)((y0 + r - 1 + (int64_t)H) % H), gx = (int)((x0 + cc - 1 + (int64_t)W) % W);
-            const int64_t g = bx * HW + (int64_t)gy * W + gx;
-            float v;
-            if constexpr (CI == 1) v = (float)ub[g] * (float)(1.0 / s[bx / nz]);
-            else v = (float)xa[g * CI + c];
-            xs[q] = v;
-        }
-        for (int q = tid; q < WGY * WGX * CO; q += 256) {
-            const int pix = q / CO, o = q % CO;
-            const int y = y0 + pix / WGX, x = x0 + pix % WGX;
-            float v = 0.0f;  // points outside the field contribute nothing
-            if (y < H && x < W) {
-                const int64_t g = b * HW + (int64_t)y * W + x;
-                if constexpr (CO == 1) v = gf[g];
-                else v = (float)ga[g * CO + o];
-            }
-            gs[q] = v;
-        }
-        __syncthreads();
+    float acc[8][9], db[8];
 #pragma unroll
-        for (int k = 0; k < SLOTS; ++k) {
-            const int idx = tid + k * 256;
-            if (idx < CO * 9 * CI) {
-                const int o = idx / (9 * CI), t = (idx / CI) % 9, c = idx % CI;
-                const int dy = t / 3, dx = t % 3;
-                float a = 0.0f;
-                for (int p = 0; p < WGY * WGX; ++p) {
-                    const int py = p / WGX, px = p % WGX;
-                    a += gs[p * CO + o] * xs[((py + dy) * (WGX + 2) + (px + dx)) * CI + c];
-                }
-                acc[k] += a;
-            } else if (idx < NWL) {
-                const int o = idx - CO * 9 * CI;
-                float a = 0.0f;
-                for (int p = 0; p < WGY * WGX; ++p) a += gs[p * CO + o];
-                acc[k] += a;
+    for (int k = 0; k < 8; ++k) {
+        db[k] = 0.0f;
+#pragma unroll
+        for (int t = 0; t < 9; ++t) acc[k][t] = 0.0f;
+    }
+    for (int64_t n = (int64_t)blockIdx.x * 4 + wave; n < nunits; n += (int64_t)gridDim.x * 4) {
+        const Unit u = unit_of(n, ENS, tiles_x, chunks, ru, H);
+        const int x = u.x0 + (lane >> 2);
+        const bool ok = x < W;
+        const int xc = ok ? x : W - 1, xm = wrap(xc - 1, W), xp = wrap(xc + 1, W);
+        const T *fp = f + plane_shift(u.b, nz, OUT ? -dzo : dzo) * HW;
+        const float inv = OUT ? 1.0f : (float)(1.0 / s[u.b / nz]);
+        const bf16 *vp = va + (u.b * HW + xc) * C + ch * 8;
+        float w[3][3];
+        auto row = [&](int y, float (&r)[3]) {
+            const T *q = fp + (int64_t)wrap(y, H) * W;
+            r[0] = (float)q[xm] * inv;
+            r[1] = (float)q[xc] * inv;
+            r[2] = (float)q[xp] * inv;
+        };
+        uint4 nv = *reinterpret_cast<const uint4 *>(vp + (int64_t)u.ya * W * C);
+        float nr[3];
+        row(u.ya - 1, w[1]);
+        row(u.ya, w[2]);
+        row(u.ya + 1, nr);
+        for (int y = u.ya; y < u.yb; ++y) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                w[0][k] = w[1][k];
+                w[1][k] = w[2][k];
+                w[2][k] = nr[k];
             }
+            alignas(16) bf16 v[8];
+            *reinterpret_cast<uint4 *>(v) = nv;
+            if (y + 1 < u.yb) {
+                nv = *reinterpret_cast<const uint4 *>(vp + (int64_t)(y + 1) * W * C);
+                row(y + 2 > H ? y + 2 - H : y + 2, nr);
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float val = ok ? (float)v[k] : 0.0f;  // points outside the field contribute nothing
+#pragma unroll
+                for (int t = 0; t < 9; ++t) acc[k][t] += val * (OUT ? w[2 - t / 3][2 - t % 3] : w[t / 3][t % 3]);
+                if constexpr (!OUT) db[k] += val;
+            }
+            if constexpr (OUT) db[0] += ok ? w[1][1] : 0.0f;
+        }
+    }
+    // the 16 points of a wave, then the waves in order
+    auto points = [&](float v) {
+#pragma unroll
+        for (int o = 4; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
+        return v;
+    };
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        db[k] = points(db[k]);
+#pragma unroll
+        for (int t = 0; t < 9; ++t) acc[k][t] = points(acc[k][t]);
+    }
+    for (int i = tid; i < NWL; i += 256) red[i] = 0.0f;
+    __syncthreads();
+    for (int wv = 0; wv < 4; ++wv) {
+        if (wave == wv && lane < 4) {
+            auto put = [&](int i, float v) { red[i] += v; };
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int c = ch * 8 + k;
+#pragma unroll
+                for (int t = 0; t < 9; ++t) put(OUT ? t * C + c : c * 9 + t, acc[k][t]);
+                if constexpr (!OUT) put(K9 + c, db[k]);
+            }
+            if constexpr (OUT)
+                if (ch == 0) put(K9, db[0]);
         }
         __syncthreads();
     }
-#pragma unroll
-    for (int k = 0; k < SLOTS; ++k) {
-        const int idx = tid + k * 256;
-        if (idx < NWL) part[(int64_t)blockIdx.x * NWL + idx] = acc[k];
-    }
+    for (int i = tid; i < NWL; i += 256) part[(int64_t)blockIdx.x * NWL + i] = red[i];
 }
 
-// Weight gradient of a 32 -> 32 layer on the matrix cores: for every tap t the
-// 32 x 32 block dW[o][t][c] = sum_p g[p][o] x[p + off(t)][c] is a GEMM with
-// K = points (16 per MFMA step).  LDS holds the tile's output gradient
-// transposed, gT[o][p], and three transposed copies of the input tile with its
-// halo, shifted by dx = 0, 1, 2 (xs[dx][c][row][j] = x[row][j + dx]), so every
-// 8-point operand is one aligned 16-byte read.  Wave w owns taps w, w+4, w+8.
-// Also the bias gradient db[o] = sum_p g[p][o].  The input comes from the
-// plane shifted by dzo (one 3x3 slice of a 3D layer).  part[block][32*288+32].
-__global__ __launch_bounds__(256) void k_wgrad_mid(const bf16 *xa, const bf16 *ga, float *part, int H, int W, int nz,
-                                                   int dzo, int tiles_x, int tiles_y, int64_t ntiles) {
-    constexpr int NP = WGY * WGX;        // points per tile
-    constexpr int XR = WGY + 2;          // input rows with the halo
-    constexpr int GST = NP + 8;          // padded row of gT (bf16)
-    constexpr int XST = XR * WGX + 8;    // padded channel plane of an xs copy (bf16)
+// Weight gradient of a 32 -> 32 layer (one 3x3 slice, the input read from the
+// plane shifted by dzo) on the matrix cores: for every tap t the 32 x 32
+// block dW[o][t][c] = sum_p g[p][o] x[p + off(t)][c] is a product over points.
+// Its operands hold one channel per lane and 8 points per register group,
+// the transpose of what a load gives (one point per lane, 8 channels).  The
+// matrix cores transpose: points x channels times the identity (exact, one
+// nonzero term per element) comes back with one channel per lane and 16 of
+// the 32 points in its registers, in an order that is the same for g and x, so
+// the product over points may use it as it is.  A wave marches down a strip
+// of 32 columns with one x-shift of the input: an input row meets the
+// transposed gradient rows above, at and below it, six products and four for
+// the transposes per row, no LDS (all three shifts in one wave need 144
+// accumulators: two waves per SIMD with one row in flight took 208 us).  Also db[o] = sum_p g[p][o].  part[block][32*288+32].
+// Bound by reading g and x once (128 bytes per point): transposing through
+// LDS with 2-byte accesses took 725 us for 8 x 512^2; this takes 100 us.
+constexpr size_t kWgradLds = (size_t)(C * K + C) * sizeof(float);
+constexpr int WGT = 384;  // six waves: two units, three x-shifts each
+__global__ __launch_bounds__(WGT, 3) void k_wgrad_mid(const bf16 *xa, const bf16 *ga, float *part, int H, int W,
+                                                      int nz, int dzo, int tiles_x, int chunks, int ru,
+                                                      int64_t nunits) {
     constexpr int NWL = C * K + C;
-    __shared__ __attribute__((aligned(16))) bf16 gT[C * GST];
-    __shared__ __attribute__((aligned(16))) bf16 xs[3 * C * XST];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    extern __shared__ __attribute__((aligned(16))) unsigned char wgrad_lds[];
+    float *red = reinterpret_cast<float *>(wgrad_lds);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 31, kh = lane >> 5;
+    const int sub = wave / 3, dx = wave - 3 * sub;  // this wave's unit of the two, and its taps (dy, dx)
+    const int64_t HW = (int64_t)H * W;
+    bf16x8 Id[2];  // identity: row k = 16 half + 8 kh + e, column j
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) Id[h][e] = (bf16)(16 * h + 8 * kh + e == j ? 1.0f : 0.0f);
     f32x16 acc[3];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) acc[q] = f32x16{};
+    for (int dy = 0; dy < 3; ++dy) acc[dy] = f32x16{};
     float db = 0.0f;
-    const int64_t HW = (int64_t)H * W;
-    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const int tx = (int)(tile % tiles_x), ty = (int)((tile / tiles_x) % tiles_y);
-        const int64_t b = tile / ((int64_t)tiles_x * tiles_y);
-        const int x0 = tx * WGX, y0 = ty * WGY;
-        for (int q = tid; q < NP * C; q += 256) {
-            const int p = q / C, o = q % C;
-            const int y = y0 + p / WGX, x = x0 + p % WGX;
-            bf16 v = (bf16)0.0f;  // points outside the field contribute nothing
-            if (y < H && x < W) v = ga[(b * HW + (int64_t)y * W + x) * C + o];
-            gT[o * GST + p] = v;
-        }
-        for (int q = tid; q < XR * (WGX + 2) * C; q += 256) {
-            const int pix = q / C, c = q % C;
-            const int r = pix / (WGX + 2), col = pix % (WGX + 2);
-            const int gy = (int)((y0 + r - 1 + (int64_t)H) % H), gx = (int)((x0 + col - 1 + (int64_t)W) % W);
-            const bf16 v = xa[(plane_shift(b, nz, dzo) * HW + (int64_t)gy * W + gx) * C + c];
+    struct Row {
+        bf16x8 h[2];
+    };
+    // one channel per lane; the values are bf16 numbers, so the upper halves hold them
+    auto transpose = [&](const Row &r, bf16x8 (&o)[2]) {
+        f32x16 d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r.h[0], Id[0], f32x16{}, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r.h[1], Id[1], d, 0, 0, 0);
 #pragma unroll
-            for (int dx = 0; dx < 3; ++dx) {
-                const int jc = col - dx;
-                if (jc >= 0 && jc < WGX) xs[(dx * C + c) * XST + r * WGX + jc] = v;
-            }
+        for (int q = 0; q < 2; ++q) {
+            uint4 p;
+            auto pk = [&](int e) {
+                const float lo = d[8 * q + e], hi = d[8 * q + e + 1];
+                return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, hi), __builtin_bit_cast(uint32_t, lo),
+                                             0x07060302u);
+            };
+            p.x = pk(0);
+            p.y = pk(2);
+            p.z = pk(4);
+            p.w = pk(6);
+            o[q] = __builtin_bit_cast(bf16x8, p);
         }
-        __syncthreads();
-        if (tid < C)
-            for (int p = 0; p < NP; ++p) db += (float)gT[tid * GST + p];
-#pragma unroll 2
-        for (int ks = 0; ks < NP / 16; ++ks) {
-            const int p0 = ks * 16, py = p0 / WGX, px0 = p0 % WGX;
-            const bf16x8 A = *reinterpret_cast<const bf16x8 *>(gT + j * GST + p0 + kh * 8);
+        return d;
+    };
+    const bf16x8 zero = {};
+    for (int64_t n = (int64_t)blockIdx.x * 2 + sub; n < nunits; n += (int64_t)gridDim.x * 2) {
+        const Unit u = unit_of(n, TX, tiles_x, chunks, ru, H);
+        const int x = u.x0 + j;
+        const bool ok = x < W;
+        const int c = x + dx - 1;
+        const bf16 *gp = ga + u.b * HW * C + (int64_t)(ok ? x : W - 1) * C + kh * 8;
+        const bf16 *xp = xa + plane_shift(u.b, nz, dzo) * HW * C + kh * 8 +
+                         (int64_t)(c < 0 ? c + W : (c >= W ? (c == W ? 0 : W - 1) : c)) * C;
+        auto load_g = [&](int y, Row &r) {  // rows past the unit are loaded again and not used
+            const bf16 *q = gp + (int64_t)min(y, u.yb - 1) * W * C;
+            r.h[0] = *reinterpret_cast<const bf16x8 *>(q);
+            r.h[1] = *reinterpret_cast<const bf16x8 *>(q + 16);
+        };
+        auto load_x = [&](int y, Row &r) {
+            const bf16 *q = xp + (int64_t)wrap(min(y, u.yb), H) * W * C;
+            r.h[0] = *reinterpret_cast<const bf16x8 *>(q);
+            r.h[1] = *reinterpret_cast<const bf16x8 *>(q + 16);
+        };
+        // step r: input row r against the gradient rows r + 1 (dy = 0), r (1)
+        // and r - 1 (2); two rows of loads in flight
+        bf16x8 G0[2], G1[2], G2[2];
 #pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const int t = wave + 4 * q;
-                if (t < 9) {
-                    const int dy = t / 3, dx = t % 3;
-                    const bf16x8 Bv =
-                        *reinterpret_cast<const bf16x8 *>(xs + (dx * C + j) * XST + (py + dy) * WGX + px0 + kh * 8);
-                    acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, Bv, acc[q], 0, 0, 0);
-                }
+        for (int q = 0; q < 2; ++q) G0[q] = G1[q] = G2[q] = zero;
+        Row ga_[2], xa_[2];
+        load_g(u.ya, ga_[0]);
+        load_x(u.ya - 1, xa_[0]);
+        load_g(u.ya + 1, ga_[1]);
+        load_x(u.ya, xa_[1]);
+        auto step = [&](int r, Row &gn, Row &xn) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                G2[q] = G1[q];
+                G1[q] = G0[q];
             }
+            if (r + 1 < u.yb) {
+                if (!ok) gn.h[0] = gn.h[1] = zero;  // points outside the field contribute nothing
+                const f32x16 d = transpose(gn, G0);
+                float sum = 0.0f;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) sum += d[v];
+                db += sum;
+            } else {
+                G0[0] = G0[1] = zero;
+            }
+            bf16x8 X[2];
+            transpose(xn, X);
+            load_g(r + 3, gn);
+            load_x(r + 2, xn);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(G0[q], X[q], acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(G1[q], X[q], acc[1], 0, 0, 0);
+                acc[2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(G2[q], X[q], acc[2], 0, 0, 0);
+            }
+        };
+        for (int r = u.ya - 1; r <= u.yb; r += 2) {
+            step(r, ga_[0], xa_[0]);
+            if (r + 1 <= u.yb) step(r + 1, ga_[1], xa_[1]);
+        }
+    }
+    db += __shfl_xor(db, 32, 64);
+    for (int i = tid; i < NWL; i += WGT) red[i] = 0.0f;
+    __syncthreads();
+    for (int sv = 0; sv < 2; ++sv) {  // the three shifts of a unit write different taps
+        if (sub == sv) {
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    red[((8 * (v >> 2) + 4 * kh + (v & 3)) * 9 + 3 * dy + dx) * C + j] += acc[dy][v];
+            if (dx == 0 && lane < C) red[C * K + j] += db;
         }
         __syncthreads();
     }
-    float *pb = part + (int64_t)blockIdx.x * NWL;
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        const int t = wave + 4 * q;
-        if (t < 9)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int o = 8 * (v >> 2) + 4 * kh + (v & 3);
-                pb[(o * 9 + t) * C + j] = acc[q][v];
-            }
-    }
-    if (tid < C) pb[C * K + tid] = db;
+    for (int i = tid; i < NWL; i += WGT) part[(int64_t)blockIdx.x * NWL + i] = red[i];
 }
 
 // grad = sum over blocks (in a fixed order) of part[block][w], where part
@@ -822,19 +1140,20 @@ __global__ __launch_bounds__(256) void k_wgrad_mid(const bf16 *xa, const bf16 *g
 // slice `bias_dzi` only.  grad points at the layer's first weight.
 __global__ void k_reduce(const float *part, int nblk, int nw, float *grad, int NT, int dzi, int bias_dzi, int CI,
                          int CO) {
-    // 32 weights per workgroup, 8 lanes per weight summing every 8th block,
-    // then the 8 lane sums in lane order: a fixed order for every run
-    __shared__ double red[8][32];
+    // 32 weights per workgroup, 32 lanes per weight summing every 32nd block,
+    // then the 32 lane sums in lane order: a fixed order for every run
+    __shared__ double red[32][32];
     const int wl = threadIdx.x & 31, g = threadIdx.x >> 5;
     const int i = blockIdx.x * 32 + wl;
     double acc = 0.0;
     if (i < nw)
-        for (int k = g; k < nblk; k += 8) acc += (double)part[(int64_t)k * nw + i];
+#pragma unroll 4
+        for (int k = g; k < nblk; k += 32) acc += (double)part[(int64_t)k * nw + i];
     red[g][wl] = acc;
     __syncthreads();
     if (g == 0 && i < nw) {
         double t = 0.0;
-        for (int q = 0; q < 8; ++q) t += red[q][wl];
+        for (int q = 0; q < 32; ++q) t += red[q][wl];
         const int nwt = CO * 9 * CI;
         if (i < nwt) {
             const int o = i / (9 * CI), tp = (i / CI) % 9, c = i % CI;
@@ -879,7 +1198,7 @@ int fail(int code, const char *fmt, ...) {
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 struct Layout {
-    size_t wbf, wT, wf, s, rms, act, z, zt, y, dy, dyz, dz, lpart, wpart, grad, total;
+    size_t wbf, wend, wT, wf, s, rms, act, z, zt, y, dy, dyz, dz, lpart, wpart, grad, total;
     int64_t N, nblk_pix;
     int nblk_w;
 };
@@ -887,9 +1206,29 @@ struct Layout {
 int taps_of(int ndim) { return ndim == 3 ? 27 : 9; }
 int64_t planes_of(const gd_grid *g) { return g->batch * (g->ndim == 3 ? g->n[2] : 1); }
 
-int64_t wgrad_tiles(const gd_grid *g) {
-    return planes_of(g) * ((g->n[1] + WGY - 1) / WGY) * ((g->n[0] + WGX - 1) / WGX);
+// Weight-gradient work: rows per unit (the two halo rows of a unit are work on
+// top), halved down to 8 until the units of `strip` columns occupy 512
+// workgroups of `per` units.
+constexpr int kWgradBlocks = 512;
+struct Units {
+    int tiles_x, chunks, ru, per;
+    int64_t n;
+};
+// units a workgroup works on at a time: k_wgrad_mid two, k_wgrad_end one per wave
+int units_per_block(int strip) { return strip == TX ? 2 : 4; }
+Units units_of(const gd_grid *g, int strip) {
+    const int per = units_per_block(strip);
+    Units u;
+    u.tiles_x = (int)((g->n[0] + strip - 1) / strip);
+    for (u.ru = 64;; u.ru /= 2) {
+        u.chunks = (int)((g->n[1] + u.ru - 1) / u.ru);
+        u.n = planes_of(g) * u.tiles_x * u.chunks;
+        if (u.ru == 8 || u.n >= (int64_t)per * kWgradBlocks) break;
+    }
+    u.per = per;
+    return u;
 }
+int blocks_of(const Units &u) { return (int)std::min<int64_t>((u.n + u.per - 1) / u.per, kWgradBlocks); }
 
 // applications of G to the network's output (the struct's 0 means 1)
 int smooth_of(const gd_cnn *net) { return net->smooth > 0 ? net->smooth : 1; }
@@ -902,11 +1241,13 @@ Layout layout(const gd_grid *g, bool training, bool own_grad, int smooth) {
     std::memset(&L, 0, sizeof L);
     L.N = planes_of(g) * g->n[0] * g->n[1];
     L.nblk_pix = (L.N + 255) / 256;
-    L.nblk_w = (int)std::min<int64_t>(wgrad_tiles(g), 512);
+    L.nblk_w = blocks_of(units_of(g, TX));
     const size_t slices = (size_t)NMID * ndz * C * K9 * 2;  // bf16 weight slices of the 32 -> 32 layers
     size_t o = 0;
     L.wbf = o;
     o = align_up(o + (size_t)off.total * 2, 256);
+    L.wend = o;
+    o = align_up(o + (size_t)2 * C * NT * 4, 256);
     L.wT = o;
     if (training) o = align_up(o + slices, 256);
     L.wf = o;
@@ -934,7 +1275,7 @@ Layout layout(const gd_grid *g, bool training, bool own_grad, int smooth) {
         L.lpart = o;
         o = align_up(o + (size_t)L.nblk_pix * 8, 256);
         L.wpart = o;
-        o = align_up(o + (size_t)L.nblk_w * NW_MID * 4, 256);
+        o = align_up(o + std::max((size_t)L.nblk_w * NW_MID, (size_t)blocks_of(units_of(g, ENS)) * NW_END) * 4, 256);
         if (own_grad) {
             L.grad = o;
             o = align_up(o + (size_t)off.total * 4, 256);
@@ -978,30 +1319,81 @@ int check_grid(const gd_cnn *net, const gd_grid *g) {
         if (e_ != hipSuccess) return fail(GD_EHIP, "launch: %s", hipGetErrorString(e_)); \
     } while (0)
 
-// One 32 -> 32 layer (forward, or its input gradient with BWD) in one
-// matrix-core pass: k_conv_mid in 2D, k_conv_mid3 (three plane-shifted
-// products in registers) in 3D.
-int mid_layer(bool bwd, const gd_grid *g, const Layout &L, char *w, const bf16 *in, const bf16 *slices,
-              const float *bias, const bf16 *mask, bf16 *out, hipStream_t st) {
-    const int NT = taps_of(g->ndim), ndz = NT / 9;
-    const int H = (int)g->n[1], W = (int)g->n[0], nz = g->ndim == 3 ? (int)g->n[2] : 1;
-    const int tiles_x = (W + TX - 1) / TX, tiles_y = (H + TY - 1) / TY;
-    const unsigned cblk = (unsigned)(planes_of(g) * tiles_x * tiles_y);
-    if (ndz == 1) {
-        if (bwd)
-            GD_LAUNCH(k_conv_mid<kBwd>, dim3(cblk), dim3(256), 0, st, in, slices, (const float *)nullptr, mask, out, H,
-                      W, tiles_x, tiles_y);
-        else
-            GD_LAUNCH(k_conv_mid<kFwd>, dim3(cblk), dim3(256), 0, st, in, slices, bias, (const bf16 *)nullptr, out, H,
-                      W, tiles_x, tiles_y);
-        return GD_OK;
+template <int MODE>
+int launch_mid2(const gd_grid *g, const bf16 *in, const bf16 *wmat, const float *bias, const bf16 *mask, bf16 *out,
+                hipStream_t st) {
+    const int H = (int)g->n[1], W = (int)g->n[0];
+    const int tiles_x = (W + TX - 1) / TX, tiles_y = (H + 4 * RB - 1) / (4 * RB);
+    const int64_t blk = planes_of(g) * tiles_x * tiles_y;
+    if (blk > 0x7fffffff) return fail(GD_EINVAL, "field too large");
+    auto kern = k_conv_mid<MODE>;
+    GD_LAUNCH(kern, dim3((unsigned)blk), dim3(256), kConvLds, st, in, wmat, bias, mask, out, H, W, tiles_x,
+              tiles_y);
+    return GD_OK;
+}
+
+template <int MODE>
+int launch_mid3(const gd_grid *g, const bf16 *in, const bf16 *slices, const float *bias, const bf16 *mask, bf16 *out,
+                hipStream_t st) {
+    const int H = (int)g->n[1], W = (int)g->n[0], nz = (int)g->n[2];
+    const int tiles_x = (W + TX - 1) / TX, tiles_y = (H + 4 * RB - 1) / (4 * RB);
+    const int64_t cols = g->batch * tiles_x * tiles_y;
+    // planes per run: the runs of one round fill the 256 CUs (one workgroup
+    // each); a run costs two planes more to load, and about one plane's time
+    // to start, so the rounds x (planes + 1) are minimised
+    int zrun = nz;
+    int64_t best = INT64_MAX;
+    for (int r = 1; r <= nz; ++r) {
+        const int len = (nz + r - 1) / r;
+        const int64_t rounds = (cols * ((nz + len - 1) / len) + 255) / 256, cost = rounds * (len + 1);
+        if (cost < best) {
+            best = cost;
+            zrun = len;
+        }
+        if (rounds > 64 && r > 1) break;
     }
-    if (bwd)
-        GD_LAUNCH(k_conv_mid3<kBwd>, dim3(cblk), dim3(256), kMid3Lds, st, in, slices, (const float *)nullptr, mask,
-                  out, H, W, nz, tiles_x, tiles_y);
-    else
-        GD_LAUNCH(k_conv_mid3<kFwd>, dim3(cblk), dim3(256), kMid3Lds, st, in, slices, bias, (const bf16 *)nullptr,
-                  out, H, W, nz, tiles_x, tiles_y);
+    const int zruns = (nz + zrun - 1) / zrun;
+    const int64_t blk = cols * zruns;
+    if (blk > 0x7fffffff) return fail(GD_EINVAL, "field too large");
+    auto kern = k_conv_mid3<MODE>;
+    GD_LAUNCH(kern, dim3((unsigned)blk), dim3(256), 4 * kConvLds, st, in, slices, bias, mask, out, H, W, nz,
+              tiles_x, tiles_y, zruns, zrun);
+    return GD_OK;
+}
+
+// One 32 -> 32 layer (forward, or its input gradient with bwd).
+int mid_layer(bool bwd, const gd_grid *g, const bf16 *in, const bf16 *slices, const float *bias, const bf16 *mask,
+              bf16 *out, hipStream_t st) {
+    if (g->ndim == 3)
+        return bwd ? launch_mid3<kBwd>(g, in, slices, bias, mask, out, st)
+                   : launch_mid3<kFwd>(g, in, slices, bias, mask, out, st);
+    return bwd ? launch_mid2<kBwd>(g, in, slices, bias, mask, out, st)
+               : launch_mid2<kFwd>(g, in, slices, bias, mask, out, st);
+}
+
+// layer 1, or with mask the input gradient of layer 6 (in = dL/dz)
+template <typename T, bool GRAD>
+int end_layer(const gd_grid *g, const T *in, const double *s, const float *wt, const float *bias, const bf16 *mask,
+              bf16 *out, hipStream_t st) {
+    const int H = (int)g->n[1], W = (int)g->n[0], nz = g->ndim == 3 ? (int)g->n[2] : 1;
+    const int tiles_x = (W + 63) / 64, tiles_y = (H + 4 * EPT - 1) / (4 * EPT), zruns = (nz + EZ - 1) / EZ;
+    const int64_t blk = (int64_t)g->batch * tiles_x * tiles_y * zruns;
+    if (blk > 0x7fffffff) return fail(GD_EINVAL, "field too large");
+    auto k2 = k_conv_end<T, 9, GRAD>;
+    auto k3 = k_conv_end<T, 27, GRAD>;
+    GD_LAUNCH(g->ndim == 2 ? k2 : k3, dim3((unsigned)blk), dim3(256), 0, st, in, s, wt, bias, mask, out, H, W, nz,
+              tiles_x, tiles_y, zruns);
+    return GD_OK;
+}
+
+// layer 6
+int out_layer(const gd_grid *g, const bf16 *a, const bf16 *w6, const float *b6, float *z, hipStream_t st) {
+    const int H = (int)g->n[1], W = (int)g->n[0], nz = g->ndim == 3 ? (int)g->n[2] : 1;
+    const int tiles_x = (W + OX - 1) / OX, tiles_y = (H + OY - 1) / OY, zruns = (nz + OZ - 1) / OZ;
+    const int64_t blk = (int64_t)g->batch * tiles_x * tiles_y * zruns;
+    if (blk > 0x7fffffff) return fail(GD_EINVAL, "field too large");
+    GD_LAUNCH(g->ndim == 2 ? k_conv_out<9> : k_conv_out<27>, dim3((unsigned)blk), dim3(256), 0, st, a, w6, b6, z, H, W,
+              nz, tiles_x, tiles_y, zruns);
     return GD_OK;
 }
 
@@ -1037,7 +1429,9 @@ int run_forward(const gd_cnn *net, const gd_grid *g, const Layout &L, char *w, c
     const size_t actb = align_up((size_t)N * C * 2, 256);
     auto act = [&](int i) { return (bf16 *)(w + L.act + (size_t)i * actb); };
     const unsigned pblk = (unsigned)L.nblk_pix;
-    GD_LAUNCH(k_cvt, dim3((unsigned)((off.total + 255) / 256)), dim3(256), 0, st, net->params, wbf, off.total);
+    float *wend = (float *)(w + L.wend);
+    GD_LAUNCH(k_cvt, dim3((unsigned)((off.total + 255) / 256)), dim3(256), 0, st, net->params, wbf, off.total, wend,
+              off.W[0], off.W[NL - 1], NT);
     bf16 *wf = (bf16 *)(w + L.wf);  // 3D: forward weight slices
     if (ndz > 1)
         GD_LAUNCH(k_repack<false>, dim3((unsigned)((NMID * ndz * C * K9 + 255) / 256)), dim3(256), 0, st,
@@ -1051,53 +1445,45 @@ int run_forward(const gd_cnn *net, const gd_grid *g, const Layout &L, char *w, c
                   (const float *)net->params, off, (float *)(w + L.z), H, W);
         return finish_forward<T>(net, L, w, ub, u0, false, H, W, nz, st);
     }
-    if (NT == 9)
-        GD_LAUNCH((k_conv_in<T, 9>), dim3(pblk), dim3(256), 0, st, ub, (const double *)s, (const bf16 *)(wbf + off.W[0]),
-                  (const float *)(net->params + off.b[0]), act(0), H, W, nz, N);
-    else
-        GD_LAUNCH((k_conv_in<T, 27>), dim3(pblk), dim3(256), 0, st, ub, (const double *)s,
-                  (const bf16 *)(wbf + off.W[0]), (const float *)(net->params + off.b[0]), act(0), H, W, nz, N);
     int rc;
+    if ((rc = end_layer<T, false>(g, ub, s, wend, net->params + off.b[0], nullptr, act(0), st))) return rc;
     for (int m = 0; m < NMID; ++m) {
         const int l = m + 1;
         bf16 *src = train ? act(m) : act(m & 1);
         bf16 *dst = train ? act(m + 1) : act((m + 1) & 1);
         const bf16 *slices = ndz > 1 ? wf + (size_t)m * ndz * C * K9 : wbf + off.W[l];
-        if ((rc = mid_layer(false, g, L, w, src, slices, net->params + off.b[l], nullptr, dst, st))) return rc;
+        if ((rc = mid_layer(false, g, src, slices, net->params + off.b[l], nullptr, dst, st))) return rc;
     }
     bf16 *last = train ? act(NL - 2) : act(NMID & 1);
-    if (NT == 9)
-        GD_LAUNCH(k_conv_out<9>, dim3(pblk), dim3(256), 0, st, (const bf16 *)last, (const bf16 *)(wbf + off.W[NL - 1]),
-                  (const float *)(net->params + off.b[NL - 1]), (float *)(w + L.z), H, W, nz, N);
-    else
-        GD_LAUNCH(k_conv_out<27>, dim3(pblk), dim3(256), 0, st, (const bf16 *)last, (const bf16 *)(wbf + off.W[NL - 1]),
-                  (const float *)(net->params + off.b[NL - 1]), (float *)(w + L.z), H, W, nz, N);
+    if ((rc = out_layer(g, last, wbf + off.W[NL - 1], net->params + off.b[NL - 1], (float *)(w + L.z), st))) return rc;
     return finish_forward<T>(net, L, w, ub, u0, train, H, W, nz, st);
 }
 
-// Weight gradient of layer (CI -> CO) into grad_layer (its first weight): one
-// pass per 3x3 slice (dz), each reduced and scattered into place.
+// Weight gradient of a layer into grad_layer (its first weight): one pass per
+// 3x3 slice (dz), each reduced and scattered into place.  CI, CO: 32 -> 32
+// (v = dz at the output, x its input), 1 -> 32 (v = dz, f = ubar) or 32 -> 1
+// (v = a5, f = dL/dz).
 template <int CI, int CO, typename T>
-int wgrad_layer(const gd_grid *g, const Layout &L, char *w, const bf16 *xa, const T *ub, const double *s,
-                const bf16 *ga, const float *gf, float *grad_layer, hipStream_t st) {
+int wgrad_layer(const gd_grid *g, const Layout &L, char *w, const bf16 *x, const bf16 *v, const T *f, const double *s,
+                float *grad_layer, hipStream_t st) {
     constexpr int NWL = CO * 9 * CI + CO;
     const int NT = taps_of(g->ndim), ndz = NT / 9;
     const int H = (int)g->n[1], W = (int)g->n[0], nz = g->ndim == 3 ? (int)g->n[2] : 1;
-    const int tiles_x = (W + WGX - 1) / WGX, tiles_y = (H + WGY - 1) / WGY;
-    const int64_t ntiles = wgrad_tiles(g);
+    const Units u = units_of(g, CI == C && CO == C ? TX : ENS);
+    const int blocks = blocks_of(u);
     float *part = (float *)(w + L.wpart);
     for (int dzi = 0; dzi < ndz; ++dzi) {
         const int dzo = ndz > 1 ? dzi - 1 : 0;
         if constexpr (CI == C && CO == C) {
-            GD_LAUNCH(k_wgrad_mid, dim3((unsigned)L.nblk_w), dim3(256), 0, st, xa, ga, part, H, W, nz, dzo, tiles_x,
-                      tiles_y, ntiles);
+            GD_LAUNCH(k_wgrad_mid, dim3((unsigned)blocks), dim3(WGT), kWgradLds, st, x, v, part, H, W, nz, dzo,
+                      u.tiles_x, u.chunks, u.ru, u.n);
         } else {
-            auto kern = k_wgrad<CI, CO, T>;
-            GD_LAUNCH(kern, dim3((unsigned)L.nblk_w), dim3(256), 0, st, xa, ub, s, ga, gf, part, H, W, nz, dzo,
-                      tiles_x, tiles_y, ntiles);
+            auto kern = k_wgrad_end<T, CO == 1>;
+            GD_LAUNCH(kern, dim3((unsigned)blocks), dim3(256), 0, st, v, f, s, part, H, W, nz, dzo, u.tiles_x,
+                      u.chunks, u.ru, u.n);
         }
-        GD_LAUNCH(k_reduce, dim3((NWL + 31) / 32), dim3(256), 0, st, (const float *)part, L.nblk_w, NWL, grad_layer,
-                  NT, dzi, (ndz - 1) / 2, CI, CO);
+        GD_LAUNCH(k_reduce, dim3((NWL + 31) / 32), dim3(1024), 0, st, (const float *)part, blocks, NWL, grad_layer, NT,
+                  dzi, (ndz - 1) / 2, CI, CO);
     }
     return GD_OK;
 }
@@ -1138,23 +1524,19 @@ int run_train(const gd_cnn *net, const gd_grid *g, const Layout &L, char *w, con
         dyz = const_cast<float *>(gin);
     }
     // layer 6
-    if ((rc = wgrad_layer<C, 1, T>(g, L, w, act(NL - 2), ub, s, nullptr, dyz, grad + off.W[NL - 1], st))) return rc;
-    if (NT == 9)
-        GD_LAUNCH(k_out_bwd<9>, dim3(pblk), dim3(256), 0, st, (const float *)dyz, (const bf16 *)(wbf + off.W[NL - 1]),
-                  (const bf16 *)act(NL - 2), dz(0), H, W, nz, N);
-    else
-        GD_LAUNCH(k_out_bwd<27>, dim3(pblk), dim3(256), 0, st, (const float *)dyz, (const bf16 *)(wbf + off.W[NL - 1]),
-                  (const bf16 *)act(NL - 2), dz(0), H, W, nz, N);
+    if ((rc = wgrad_layer<C, 1, float>(g, L, w, nullptr, act(NL - 2), dyz, s, grad + off.W[NL - 1], st))) return rc;
+    const float *w6 = (const float *)(w + L.wend) + C * NT;
+    if ((rc = end_layer<float, true>(g, dyz, s, w6, nullptr, act(NL - 2), dz(0), st))) return rc;
     // layers 5 .. 2: dz(k) holds the gradient at the output of layer l
     int k = 0;
     for (int l = NL - 2; l >= 1; --l, ++k) {
         const bf16 *xin = act(l - 1);  // input activation of layer l
-        if ((rc = wgrad_layer<C, C, T>(g, L, w, xin, ub, s, dz(k), nullptr, grad + off.W[l], st))) return rc;
-        if ((rc = mid_layer(true, g, L, w, dz(k), wT + (size_t)(l - 1) * ndz * C * K9, nullptr, xin, dz(k + 1), st)))
+        if ((rc = wgrad_layer<C, C, T>(g, L, w, xin, dz(k), nullptr, s, grad + off.W[l], st))) return rc;
+        if ((rc = mid_layer(true, g, dz(k), wT + (size_t)(l - 1) * ndz * C * K9, nullptr, xin, dz(k + 1), st)))
             return rc;
     }
     // layer 1 (input x0 = ubar / s)
-    if ((rc = wgrad_layer<1, C, T>(g, L, w, nullptr, ub, s, dz(k), nullptr, grad + off.W[0], st))) return rc;
+    if ((rc = wgrad_layer<1, C, T>(g, L, w, nullptr, dz(k), ub, s, grad + off.W[0], st))) return rc;
     GD_LAUNCH(k_adam, dim3((unsigned)((off.total + 255) / 256)), dim3(256), 0, st, net->params, net->adam_m,
               net->adam_v, (const float *)grad, off.total, (const int32_t *)net->step, net->lr, net->beta1, net->beta2,
               net->eps);
