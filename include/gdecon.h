@@ -271,7 +271,9 @@ typedef struct gd_tune_info {
                                 as many as keep every resident wave busy.
                                 Uniform solves only (uneven batches ignore
                                 it); the tuner tries it for 3D fields. */
-    int32_t pad;
+    int32_t resident;        /* 1: the field is solved in the chip's registers,
+                                where the choices above do not apply (fields
+                                too large for it use them) */
     double best_ms;          /* trial time of the chosen configuration (the
                                 leaders' round: solves of 8 Krylov or 20 Van
                                 Cittert / steepest-descent passes) */
@@ -287,7 +289,7 @@ int deconvolve_batch_autotune(int32_t solver, int32_t dtype, const gd_instance *
  * reproducible runs): later solves with the same solver, grid and pointer
  * alignment (the alignment of ubar and u decides the lane width), or the same
  * instance list, use `choice` (its tiles_per_wave, rows, tail_pct,
- * interleave, wave_claims, blocks_per_cu and segments; the timing fields are ignored).  Also written to the
+ * interleave, wave_claims, blocks_per_cu, segments and, in gd_tune_set, resident; the timing fields are ignored).  Also written to the
  * GD_TUNE_CACHE file when it is set.  Errors: GD_EINVAL. */
 int gd_tune_set(int32_t solver, const gd_grid *grid, const void *ubar, const void *u, const gd_tune_info *choice);
 int gd_tune_set_batch(int32_t solver, int32_t dtype, const gd_instance *list, int32_t count,

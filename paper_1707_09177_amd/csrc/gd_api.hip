@@ -19,6 +19,7 @@
 
 #include "gd_internal.h"
 #include "gd_kernels.h"
+#include "gd_resident.h"
 #include "gdecon.h"
 
 namespace gd {
@@ -370,12 +371,14 @@ void tune_load_locked() {
     char line[1024];
     while (fgets(line, sizeof line, fp)) {
         char key[900];
-        int tpw = 0, rows = 0, tail = 0, ilv = 0, wc = 0, bpc = kBlocksPerCu, segs = 0;
-        const int nf = sscanf(line, "%899s %d %d %d %d %d %d %d", key, &tpw, &rows, &tail, &ilv, &wc, &bpc, &segs);
+        int tpw = 0, rows = 0, tail = 0, ilv = 0, wc = 0, bpc = kBlocksPerCu, segs = 0, res = 0;
+        const int nf =
+            sscanf(line, "%899s %d %d %d %d %d %d %d %d", key, &tpw, &rows, &tail, &ilv, &wc, &bpc, &segs, &res);
         if (nf >= 6 && tpw >= 1 && tpw <= 64 && rows >= 0 && rows <= 4 && tail >= 0 && tail <= 50 &&
             (ilv == 0 || ilv == 1) && (wc == 0 || wc == 1) && bpc >= 0 && bpc <= kMaxBlocksPerCu && segs >= 0 &&
-            segs <= kMaxSegs) {
+            segs <= kMaxSegs && (res == 0 || res == 1)) {
             TuneCfg c;
+            c.res = res;
             c.tpw = tpw;
             c.rows = rows;
             c.tail = tail;
@@ -404,7 +407,8 @@ void tune_store(const std::string &key, const TuneCfg &c) {
     g_tune[key] = c;
     if (const char *f = tune_file()) {
         if (FILE *fp = fopen(f, "a")) {
-            fprintf(fp, "%s %d %d %d %d %d %d %d\n", key.c_str(), c.tpw, c.rows, c.tail, c.ilv, c.wc, c.bpc, c.segs);
+            fprintf(fp, "%s %d %d %d %d %d %d %d %d\n", key.c_str(), c.tpw, c.rows, c.tail, c.ilv, c.wc, c.bpc, c.segs,
+                    c.res);
             fclose(fp);
         }
     }
@@ -466,6 +470,23 @@ int solve_uniform(int solver, const gd_grid *g, const void *ubar, void *u, const
     TuneCfg cfg;
     if (force) cfg = *force;
     else tune_lookup(key_uniform(solver, g, aligned) + (spec ? ":spec" : ""), &cfg);
+    // A field whose vectors fit the chip's registers is solved there: a pass
+    // costs its reductions and boundary exchanges instead of 4 to 15 field
+    // accesses and a grid barrier per sweep (gd_resident_kernel.h).  Not while
+    // barrier timestamps are recorded or GD_STEAL pins the tile schedule.
+    if (stage == UNI_ALL && !spec && cfg.res && !g_trace && !getenv("GD_STEAL")) {
+        DevProps dp;
+        if ((rc = dev_props(&dp))) return rc;
+        gdres::Plan plan;
+        const size_t vec_total = (size_t)nvec_of(solver) * vec_bytes;
+        if (gdres::plan(solver, g->ndim, nx, ny, nz, (int)tsize, dp.ncu, &plan) &&
+            gdres::scratch_ok(plan, g->batch, dp.ncu, field_bytes, vec_total)) {
+            const int64_t ticks = wait_ticks_of(o);
+            return gdres::solve(solver, g, plan, grid_weight(g), ubar, u, o, replacements_of(o),
+                                ticks > 0 ? ticks : (int64_t)10 * 1000 * dp.wall_khz, dp.ncu, (char *)work + off_vec,
+                                field_bytes, vec_total, info, (hipStream_t)stream);
+        }
+    }
     TileShape ts = choose_tiles(g->ndim, nx, ny, nz, g->batch, (int)tsize, aligned, solver, false);
     if (g->ndim == 3 && cfg.rows > 0 && variant_ok((int)tsize, 3, ts.vw, cfg.rows) && (cfg.rows == 1 || ny >= cfg.rows))
         ts.R = cfg.rows;
@@ -880,6 +901,7 @@ int time_candidates(const std::vector<TuneCfg> &cands, Launch &&launch, hipStrea
         out->wave_claims = cands[best].wc;
         out->blocks_per_cu = cands[best].bpc;
         out->segments = cands[best].segs;
+        out->resident = cands[best].res;
         out->best_ms = best_ms;
         out->default_ms = t2.empty() ? 0.0 : t2[0];
     }
@@ -911,7 +933,8 @@ int tune_uniform(int solver, const gd_grid *g, const void *ubar, void *u, void *
     if (rc) return rc;
     if (solver < GD_VANCITTERT || solver > GD_STEEPEST_DESCENT) return fail(GD_EINVAL, "bad solver %d", solver);
     const gd_opts o = trial_opts(solver), o2 = trial_opts(solver, true);
-    std::vector<TuneCfg> cands;
+    // the untuned default, then the tile schedules of the streaming kernel
+    std::vector<TuneCfg> cands(1);
     std::vector<int> rows = {0};
     if (g->ndim == 3 && !spec) rows = {0, 1, 2, 4};
     for (int bp : kBpcCands)
@@ -921,6 +944,7 @@ int tune_uniform(int solver, const gd_grid *g, const void *ubar, void *u, void *
                     for (int il = 0; il < 2; ++il)
                         for (int wc = 0; wc < 2; ++wc) {
                             TuneCfg c;
+                            c.res = 0;
                             c.tpw = t;
                             c.rows = r;
                             c.tail = tl;
@@ -938,6 +962,7 @@ int tune_uniform(int solver, const gd_grid *g, const void *ubar, void *u, void *
             for (int r : rows)
                 for (int sg = 1; sg <= 4; ++sg) {
                     TuneCfg c;
+                    c.res = 0;
                     c.tpw = 1;
                     c.rows = r;
                     c.tail = 0;
@@ -1134,6 +1159,7 @@ int gd_tune_set(int32_t solver, const gd_grid *g, const void *ubar, const void *
     if (solver < GD_VANCITTERT || solver > GD_STEEPEST_DESCENT) return fail(GD_EINVAL, "bad solver %d", solver);
     TuneCfg cfg;
     if ((rc = tune_choice(choice, &cfg))) return rc;
+    cfg.res = choice->resident != 0;
     const bool aligned = ((uintptr_t)ubar % 16 == 0) && ((uintptr_t)u % 16 == 0);
     tune_store(key_uniform(solver, g, aligned), cfg);
     return GD_OK;

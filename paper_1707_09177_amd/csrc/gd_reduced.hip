@@ -26,6 +26,7 @@
 #include <algorithm>
 #include <cmath>
 
+#include "gd_cluster.h"
 #include "gd_kernels.h"
 #include "gd_reduced.h"
 
@@ -33,12 +34,12 @@ namespace gdred {
 
 using gd::fail;
 
+using gdcl::kMaxW;
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
 // classes per thread, so that a solver's vectors (three, four or BiCGSTAB's
 // five, in FP64) fit the 256 registers of two waves per SIMD without spilling
 constexpr int max_e(int solver) { return solver == GD_BICGSTAB ? 12 : 16; }
-constexpr int kMaxW = 256;     // workgroups per field
 constexpr int kExpand = 256;   // threads of the expand kernel
 
 // What a field's solve leaves for the expand pass.
@@ -163,93 +164,22 @@ __global__ __launch_bounds__(256) void k_fold(const T *X, Params P) {
     if (fld == 0) P.lam[j] = ghat(f, a, b, c);
 }
 
-// ------------------------------------------------------------- all-reduce
-// Sums over a field's workgroups.  A workgroup publishes its sums as 64-bit
-// words of 32 payload bits and the 32-bit number of the reduction, so a
-// word is valid by itself: no fence, no counter, one store and one load per
-// word.  Two slot sets alternate: a workgroup can only be one reduction ahead
-// of the slowest, which has then left the set before the last.  Sums are
-// taken in workgroup order: the same result in every workgroup and every run.
-struct Shared {
-    double red[2][3][kWaves];
-    uint32_t val[kMaxW * 6];
-    double tot[2][3];
-    int abort;
-};
-
-template <int N>
-__device__ bool all_sum(const Params &P, Shared &sh, int cl, int wg, uint32_t &seq, double (&v)[N]) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int par = seq & 1;
-    ++seq;
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        const double s = gd::wave_sum(v[k]);
-        if (lane == 0) sh.red[par][k][wave] = s;
-    }
-    __syncthreads();
-    if (P.W == 1) {
-#pragma unroll
-        for (int k = 0; k < N; ++k) {
-            double s = 0.0;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) s += sh.red[par][k][w];
-            v[k] = s;
-        }
-        return true;
-    }
-    uint64_t *slot = P.slot + ((int64_t)cl * 2 + par) * P.W * 6;
-    if ((int)threadIdx.x < N) {
-        double s = 0.0;
-        for (int w = 0; w < kWaves; ++w) s += sh.red[par][threadIdx.x][w];
-        const uint64_t bits = __builtin_bit_cast(uint64_t, s), tag = (uint64_t)seq << 32;
-        uint64_t *p = slot + (int64_t)wg * 6 + 2 * threadIdx.x;
-        __hip_atomic_store(p, tag | (bits & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(p + 1, tag | (bits >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    const int64_t t0 = wall_clock64();
-    for (int i = threadIdx.x; i < P.W * 2 * N; i += kThreads) {
-        const int w = i / (2 * N), k = i - w * (2 * N);
-        uint64_t *p = slot + (int64_t)w * 6 + k;
-        uint64_t x;
-        while ((uint32_t)((x = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 32) != seq) {
-            if (__hip_atomic_load(&P.ctl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ||
-                wall_clock64() - t0 > P.wait_ticks) {
-                __hip_atomic_store(&P.ctl->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                sh.abort = 1;
-                break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-        }
-        sh.val[w * 6 + k] = (uint32_t)x;
-    }
-    __syncthreads();
-    if (sh.abort) return false;
-    if (wave < N) {
-        double s = 0.0;
-        for (int w = lane; w < P.W; w += 64) {
-            const uint64_t bits = (uint64_t)sh.val[w * 6 + 2 * wave + 1] << 32 | sh.val[w * 6 + 2 * wave];
-            s += __builtin_bit_cast(double, bits);
-        }
-        s = gd::wave_sum(s);
-        if (lane == 0) sh.tot[par][wave] = s;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < N; ++k) v[k] = sh.tot[par][k];
-    return true;
-}
-
 // ------------------------------------------------------------------ solve
 // One solve per cluster of W workgroups; clusters take fields in turn.  The
 // scalars, the guards and the stopping rule are those of the persistent
 // solve kernel (update_scalars); every thread holds them.
 template <int SOLVER, int E>
 __global__ __launch_bounds__(kThreads) void k_red_solve(Params P) {
-    __shared__ Shared sh;
+    __shared__ gdcl::Shared<kWaves> sh;
     const int cl = blockIdx.x / P.W, wg = blockIdx.x % P.W;
     const int64_t K = P.f.K;
-    uint32_t seq = 0;
+    gdcl::Cluster cluster;
+    cluster.slot = P.slot + (int64_t)cl * 2 * P.W * gdcl::kWords;
+    cluster.abort = &P.ctl->abort;
+    cluster.wait_ticks = P.wait_ticks;
+    cluster.W = P.W;
+    cluster.wg = wg;
+    cluster.seq = 0;
     if (threadIdx.x == 0) sh.abort = 0;
     double lam[E], r[E], u[E];
     double p[SOLVER == GD_CG || SOLVER == GD_BICGSTAB ? E : 1], f0[SOLVER == GD_BICGSTAB ? E : 1];
@@ -276,7 +206,7 @@ __global__ __launch_bounds__(kThreads) void k_red_solve(Params P) {
             if constexpr (SOLVER == GD_CG || SOLVER == GD_BICGSTAB) p[e] = r[e];
             if constexpr (SOLVER == GD_BICGSTAB) f0[e] = r[e];
         }
-        if (!all_sum<2>(P, sh, cl, wg, seq, s0)) return;
+        if (!gdcl::all_sum<2>(cluster, sh, s0)) return;
         double rr = P.hw * s0[0], rho = rr;
         const double r0 = sqrt(rr);
         const double r_ref = (P.init == GD_INIT_UBAR && P.norm_ref == GD_REF_R0UBAR) ? r0 : sqrt(P.hw * s0[1]);
@@ -304,7 +234,7 @@ __global__ __launch_bounds__(kThreads) void k_red_solve(Params P) {
                     r[e] -= lam[e] * r[e];
                     s[0] += r[e] * r[e];
                 }
-                if (!all_sum<1>(P, sh, cl, wg, seq, s)) return;
+                if (!gdcl::all_sum<1>(cluster, sh, s)) return;
                 rr = P.hw * s[0];
                 ++iters;
                 if (hist) hist[iters] = sqrt(rr);
@@ -316,7 +246,7 @@ __global__ __launch_bounds__(kThreads) void k_red_solve(Params P) {
                     const double d = SOLVER == GD_CG ? p[e] : r[e];
                     s[0] += d * (lam[e] * d);
                 }
-                if (!all_sum<1>(P, sh, cl, wg, seq, s)) return;
+                if (!gdcl::all_sum<1>(cluster, sh, s)) return;
                 const double pd = P.hw * s[0];
                 if (!isfinite(pd)) {
                     status = GD_NONFINITE;
@@ -335,7 +265,7 @@ __global__ __launch_bounds__(kThreads) void k_red_solve(Params P) {
                     r[e] -= alpha * (lam[e] * d);
                     s[0] += r[e] * r[e];
                 }
-                if (!all_sum<1>(P, sh, cl, wg, seq, s)) return;
+                if (!gdcl::all_sum<1>(cluster, sh, s)) return;
                 const double rn = P.hw * s[0];
                 ++iters;
                 if (hist) hist[iters] = sqrt(rn);
@@ -351,7 +281,7 @@ __global__ __launch_bounds__(kThreads) void k_red_solve(Params P) {
                 double s[1] = {0.0};
 #pragma unroll
                 for (int e = 0; e < E; ++e) s[0] += f0[e] * (lam[e] * p[e]);
-                if (!all_sum<1>(P, sh, cl, wg, seq, s)) return;
+                if (!gdcl::all_sum<1>(cluster, sh, s)) return;
                 const double fq = P.hw * s[0];
                 if (!isfinite(fq)) {
                     status = GD_NONFINITE;
@@ -371,7 +301,7 @@ __global__ __launch_bounds__(kThreads) void k_red_solve(Params P) {
                     b[1] += t * t;
                     b[2] += r[e] * r[e];
                 }
-                if (!all_sum<3>(P, sh, cl, wg, seq, b)) return;
+                if (!gdcl::all_sum<3>(cluster, sh, b)) return;
                 const double st = P.hw * b[0], tt = P.hw * b[1], ss = P.hw * b[2];
                 // a sweep that ends here leaves u untouched
                 if (!isfinite(st) || !isfinite(tt) || !isfinite(ss)) {
@@ -392,7 +322,7 @@ __global__ __launch_bounds__(kThreads) void k_red_solve(Params P) {
                     c[0] += f0[e] * r[e];
                     c[1] += r[e] * r[e];
                 }
-                if (!all_sum<2>(P, sh, cl, wg, seq, c)) return;
+                if (!gdcl::all_sum<2>(cluster, sh, c)) return;
                 const double fr = P.hw * c[0];
                 rr = P.hw * c[1];
                 ++iters;
@@ -595,7 +525,7 @@ bool layout_of(const Fold &f, int solver, int64_t batch, int ncu, Layout *L) {
     };
     off = gd::align_up(off, 256);
     L->lam = take((size_t)f.K * sizeof(double));
-    L->slot = take((size_t)L->nclusters * 2 * L->W * 6 * sizeof(uint64_t));
+    L->slot = take((size_t)L->nclusters * 2 * L->W * gdcl::kWords * sizeof(uint64_t));
     L->ctl = take(sizeof(Ctl));
     L->rec = take((size_t)batch * sizeof(Rec));
     L->done = take((size_t)batch * sizeof(uint32_t));
@@ -647,7 +577,7 @@ int solve(int solver, int dtype, const Fold &f, int64_t batch, double hw, const 
     P.part = (double *)(w + L.part);
     P.batch = batch;
     P.nclusters = L.nclusters;
-    P.nslots = L.nclusters * 2 * L.W * 6;
+    P.nslots = L.nclusters * 2 * L.W * gdcl::kWords;
     P.W = (int32_t)L.W;
     P.chunks = (int32_t)L.chunks;
     P.init = o->init;

@@ -1,0 +1,125 @@
+"""The stencil solve of fields that fit the chip's registers, at the edges of
+its boxes and dispatch, against the oracle: one box and several, partial
+columns and bands, fields of one row or plane, every solver, start and dtype,
+and batches of more fields than run at once.
+
+Tolerances: the arithmetic per point is that of the streaming kernel, only
+sums are taken in another order: FP64 1e-10 relative L2 at equal pass counts,
+FP32 1e-5 against the oracle on the FP32-rounded input.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_helpers import filtered_input, gpu_solve, rel_l2_per_field, to_dev
+from paper_1707_09177_amd import gdecon
+
+pytestmark = pytest.mark.gpu
+
+RESIDENT = 10000   # variant codes of the register-resident kernels start here
+
+# one box: rows of 1, below / at / past a band of 8, a full box; several boxes:
+# partial last box, two boxes (both neighbours the same), one row per band
+SHAPES2 = [(1, 1), (2, 1), (7, 5), (8, 64), (9, 33), (64, 64), (17, 500), (70, 130), (200, 300), (333, 1000)]
+SHAPES3 = [(1, 1, 1), (2, 3, 5), (8, 9, 10), (9, 8, 7), (16, 16, 16), (17, 30, 33), (33, 40, 50), (90, 100, 97)]
+
+
+def check(solver, ub, nd, dtype, N, **kw):
+    want, winf, _ = oracle.solve(solver, ub, nd, N, **kw)
+    got, ginf, _ = gpu_solve(solver, ub, nd, N, dtype=dtype, history=False, **kw)
+    assert gdecon.last_launch()["variant"] >= RESIDENT
+    spread = 0.0
+    if dtype == torch.float64:
+        spread = max(max(rel_l2_per_field(oracle.solve(solver, ub, nd, N, sum_mode=m, **kw)[0], want, nd)) for m in (1, 2))
+    tol = max(1e-10, 20 * spread) if dtype == torch.float64 else 1e-5
+    for e in rel_l2_per_field(got, want, nd):
+        assert e <= tol, e
+    for gi, wi in zip(ginf, winf):
+        assert gi["iters"] == wi["iters"] and gi["status_name"] == wi["status_name"]
+        assert abs(gi["r_true"] - wi["r_true"]) <= max(10 * tol * wi["r_ref"], 1e-300)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("shape", SHAPES2 + SHAPES3, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("solver", ["vc", "sd", "cg", "bicgstab"])
+def test_boxes_match_oracle(solver, shape, dtype):
+    nd = len(shape)
+    u = np.random.default_rng(sum(shape)).standard_normal((2,) + shape)
+    check(solver, filtered_input(oracle.filter(u, nd), nd, dtype), nd, dtype, 3)
+
+
+@pytest.mark.parametrize("solver, shape, dtype", [
+    ("vc", (30, 1025), torch.float32), ("sd", (9, 2048), torch.float64),            # two columns per thread
+    ("cg", (40, 1500), torch.float32), ("bicgstab", (33, 1300), torch.float64), ("bicgstab", (20, 2047), torch.float32),
+    ("bicgstab", (21, 2048), torch.float64),                                        # no room for f0 in LDS
+    ("bicgstab", (128, 128, 128), torch.float64),
+    ("cg", (1100, 2000), torch.float64), ("cg", (2100, 1024), torch.float64),       # more points per thread
+    ("cg", (130, 128, 128), torch.float64), ("vc", (131, 128, 125), torch.float64), ("sd", (160, 160, 160), torch.float32),
+])
+def test_long_rows_and_large_fields(solver, shape, dtype):
+    nd = len(shape)
+    u = np.random.default_rng(sum(shape)).standard_normal((1,) + shape)
+    check(solver, filtered_input(oracle.filter(u, nd), nd, dtype), nd, dtype, 2)
+
+
+@pytest.mark.parametrize("init", ["zero", "given", "warm"])
+@pytest.mark.parametrize("norm_ref", ["r0ubar", "ubar"])
+@pytest.mark.parametrize("shape", [(40, 30), (150, 260), (12, 33, 40)], ids=lambda s: "x".join(map(str, s)))
+def test_starts_and_norms(init, norm_ref, shape):
+    nd = len(shape)
+    r = np.random.default_rng(3)
+    ub = oracle.filter(r.standard_normal((2,) + shape), nd)
+    # a good guess, and one worse than ubar
+    u0 = np.stack([ub[0] + 0.9 * (ub[0] - oracle.filter(ub[0], nd)), ub[1] + r.standard_normal(shape)])
+    check("bicgstab", ub, nd, torch.float64, 3, init=init, u0=None if init == "zero" else u0, norm_ref=norm_ref)
+
+
+def test_fields_in_rounds_equal_single_fields():
+    """Fields of 32 boxes: 20 of them run eight at a time, each as if alone, bit for bit."""
+    u = torch.randn(20, 512, 1000, device="cuda")
+    ub = gdecon.filter_apply(gdecon.filter_apply(u))
+    d = gdecon.Deconvolver(ub.shape, 2, ub.dtype, "bicgstab")
+    res = d.solve(ub, 50, 1e-5)
+    inf = res.info()
+    assert gdecon.last_launch()["variant"] >= RESIDENT
+    one = gdecon.Deconvolver(ub[:1].shape, 2, ub.dtype, "bicgstab")
+    for b in (0, 9, 19):
+        r1 = one.solve(ub[b:b + 1].contiguous(), 50, 1e-5)
+        assert torch.equal(r1.u[0], res.u[b]) and r1.info()[0] == inf[b]
+
+
+def test_pinned_schedules_and_large_fields_stream():
+    """A pinned tile schedule, and a field past the registers, use the streaming kernel."""
+    ub = gdecon.filter_apply(torch.randn(100, 120, device="cuda"))
+    d = gdecon.Deconvolver(ub.shape, 2, ub.dtype, "cg")
+    out = torch.empty_like(ub)
+    a = d.solve(ub, 5, 0.0, out=out).u.clone()
+    assert gdecon.last_launch()["variant"] >= RESIDENT
+    gdecon.tune_set("cg", ub, out)
+    try:
+        b = d.solve(ub, 5, 0.0, out=out).u
+        assert gdecon.last_launch()["variant"] < RESIDENT
+        assert float((a - b).norm() / a.norm()) <= 1e-6
+    finally:
+        gdecon.tune_reset()
+    big = gdecon.filter_apply(torch.randn(2304, 2048, device="cuda"))
+    gdecon.deconvolve("bicgstab", big, 1)
+    assert gdecon.last_launch()["variant"] < RESIDENT
+
+
+def test_capture_and_replay():
+    ub = gdecon.filter_apply(torch.randn(3, 300, 400, device="cuda", dtype=torch.float64))
+    d = gdecon.Deconvolver(ub.shape, 2, ub.dtype, "cg")
+    out = torch.empty_like(ub)
+    res = d.solve(ub, 60, 1e-8, out=out)
+    eager, info = out.clone(), res.info()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        d.solve(ub, 60, 1e-8, out=out)
+    for _ in range(3):
+        out.fill_(float("nan"))
+        (torch.randn(1 << 20, device="cuda") * 2).sum().item()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager) and res.info() == info
