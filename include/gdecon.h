@@ -289,7 +289,8 @@ int deconvolve_batch_autotune(int32_t solver, int32_t dtype, const gd_instance *
  * reproducible runs): later solves with the same solver, grid and pointer
  * alignment (the alignment of ubar and u decides the lane width), or the same
  * instance list, use `choice` (its tiles_per_wave, rows, tail_pct,
- * interleave, wave_claims, blocks_per_cu, segments and, in gd_tune_set, resident; the timing fields are ignored).  Also written to the
+ * interleave, wave_claims, blocks_per_cu, segments and, in gd_tune_set,
+ * resident; the timing fields are ignored).  Also written to the
  * GD_TUNE_CACHE file when it is set.  Errors: GD_EINVAL. */
 int gd_tune_set(int32_t solver, const gd_grid *grid, const void *ubar, const void *u, const gd_tune_info *choice);
 int gd_tune_set_batch(int32_t solver, int32_t dtype, const gd_instance *list, int32_t count,
@@ -408,9 +409,12 @@ int deconvolve_vancittert_blocked(const gd_grid *grid, const void *ubar, void *u
  *   coefficients (G diagonal there; inner products by Parseval's identity),
  *   between one forward FFT of ubar (and of u when opts->init is
  *   GD_INIT_GIVEN or GD_INIT_WARM) and one inverse FFT of the result; r_true
- *   is evaluated there too.  A GD_INIT_WARM start is band-projected on its
- *   coefficients first (band_project's P with tau = 1e-10, see below: free
- *   here), then judged against the ubar start.  Stream-ordered.
+ *   is evaluated there too.  From a GD_INIT_UBAR or GD_INIT_ZERO start every
+ *   coefficient with the same |k|^2 keeps the same factor, and the iteration
+ *   runs on one FP64 number per group of them.  A GD_INIT_WARM start is
+ *   band-projected on its coefficients first (band_project's P with
+ *   tau = 1e-10, see below: free here), then judged against the ubar start.
+ *   Stream-ordered.
  * Errors: GD_EINVAL (unsupported size, gamma <= 0, NULL, overlaps),
  * GD_EWORKSPACE, GD_EALIGN (workspace not 256-byte aligned), GD_EHIP.
  */

@@ -130,8 +130,9 @@ struct Sync {
 
 // A workgroup drains its own group's pool, then helps with the others.
 constexpr int kSteal = NGRP;
-// Target tiles per resident wave: the dynamic pools need several per wave to
-// even out the per-wave speed differences at the end of a sweep.
+// Target tiles per resident wave of uneven batches and spectral solves: the
+// dynamic pools need several per wave to even out the per-wave speed
+// differences at the end of a sweep.
 constexpr int kTilesPerWave = 2;
 // Percent of every column's planes cut into short tiles (claimed last).
 constexpr int kTailPct = 15;

@@ -123,3 +123,28 @@ def test_capture_and_replay():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, eager) and res.info() == info
+
+
+@pytest.mark.parametrize("shape", [(9, 64), (200, 130), (517, 260), (9, 4, 8), (17, 5, 30), (40, 33, 64), (8, 70, 130)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("solver", ["vc", "sd", "cg", "bicgstab"])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_streamed_long_tiles_match_oracle(solver, shape, dtype):
+    """The tiles of an untuned streaming solve (one per wave, none short, four rows in 3D)
+    on small fields, whose tiles and rows divide unevenly."""
+    nd = len(shape)
+    u = np.random.default_rng(sum(shape)).standard_normal((2,) + shape)
+    ub = filtered_input(oracle.filter(u, nd), nd, dtype)
+    want, winf, _ = oracle.solve(solver, ub, nd, 3)
+    x = to_dev(ub, dtype)
+    out = torch.empty_like(x)
+    gdecon.tune_set(solver, x, out, ndim=nd, tiles_per_wave=1, rows=4 if nd == 3 else 0, tail_pct=0)
+    try:
+        res = gdecon.Deconvolver(x.shape, nd, dtype, solver).solve(x, 3, 0.0, out=out)
+        assert gdecon.last_launch()["variant"] < RESIDENT
+    finally:
+        gdecon.tune_reset()
+    spread = max(max(rel_l2_per_field(oracle.solve(solver, ub, nd, 3, sum_mode=m)[0], want, nd)) for m in (1, 2))
+    tol = max(1e-10, 20 * spread) if dtype == torch.float64 else 1e-5
+    assert max(rel_l2_per_field(out.cpu().numpy(), want, nd)) <= tol
+    assert [i["status_name"] for i in res.info()] == [i["status_name"] for i in winf]
