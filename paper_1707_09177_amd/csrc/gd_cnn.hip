@@ -284,7 +284,7 @@ __global__ __launch_bounds__(256) void k_conv_end(const T *in, const double *s, 
 // A workgroup of four waves owns 4 RB rows x 32 columns of a plane, wave w
 // rows w RB ...  A plane's tile with its halo sits in LDS, written by
 // direct-to-LDS loads (no registers), 64 bytes per point with its chunks
-// permuted (swz).  An input row is read from LDS once (six
+// permuted (tile_at).  An input row is read from LDS once (six
 // operands: three taps, two channel halves) and used for the three output
 // rows it belongs to, with the weights in registers.  Products per output run
 // dz, dy, dx, channel half in order.
@@ -309,23 +309,28 @@ __device__ __forceinline__ int64_t xcd_order() {
     return xcd * per + (xcd < rem ? xcd : rem) + k;
 }
 
-// start the loads of a plane's tile (rows y0 - 1 .., columns x0 - 1 .., periodic) into LDS
-__device__ __forceinline__ void stage_tile(const bf16 *plane, unsigned char *tile, int x0, int y0, int H, int W,
-                                           int wave, int lane) {
-    constexpr int CH = (4 * RB + 2) * TXH * 4;
-    for (int q0 = wave * 64; q0 < CH; q0 += 256) {
-        const int q = q0 + lane;
-        if (q < CH) {
-            const int pix = q >> 2, c = (q & 3) ^ ((pix >> 1) & 3);
-            const int r = pix / TXH, cc = pix - r * TXH;
-            int gy = y0 + r - 1, gx = x0 + cc - 1;
-            gy = gy < 0 ? gy + H : (gy >= H ? (gy == H ? 0 : H - 1) : gy);  // points past the halo are not used
-            gx = gx < 0 ? gx + W : (gx >= W ? (gx == W ? 0 : W - 1) : gx);
-            __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void *)(plane + ((int64_t)gy * W + gx) * C + c * 8),
-                (__attribute__((address_space(3))) void *)(tile + (size_t)q0 * 16), 16, 0, 0);
-        }
-    }
+// chunk c (of four, 16 bytes each) of point (row, col) of a tile, in chunks.
+// The permutation depends on the column only, so that a lane's rows are one
+// address plus constants.
+__device__ __forceinline__ int tile_at(int row, int col, int c) { return (row * TXH + col) * 4 + (c ^ ((col >> 1) & 3)); }
+
+// A plane's tile (rows y0 - 1 .., columns x0 - 1 .., periodic) is loaded in
+// 16-byte pieces, piece k 256 + thread by a thread: its place in the plane, in pieces
+constexpr int CH = (4 * RB + 2) * TXH * 4, CPL = (CH + 255) / 256;  // pieces, per thread
+__device__ __forceinline__ uint32_t tile_piece(int k, int x0, int y0, int H, int W) {
+    const int q = min(k * 256 + (int)threadIdx.x, CH - 1);
+    const int pix = q >> 2, r = pix / TXH, cc = pix - r * TXH, c = (q & 3) ^ ((cc >> 1) & 3);
+    int gy = y0 + r - 1, gx = x0 + cc - 1;
+    gy = gy < 0 ? gy + H : (gy >= H ? (gy == H ? 0 : H - 1) : gy);  // points past the halo are not used
+    gx = gx < 0 ? gx + W : (gx >= W ? (gx == W ? 0 : W - 1) : gx);
+    return ((uint32_t)gy * (uint32_t)W + (uint32_t)gx) * 4 + c;
+}
+// start the load of piece k, `at` in the plane, into LDS
+__device__ __forceinline__ void stage_piece(const bf16 *plane, unsigned char *tile, int k, uint32_t at, int wave) {
+    if ((k + 1) * 256 <= CH || k * 256 + (int)threadIdx.x < CH)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(plane + (int64_t)at * 8),
+                                         (__attribute__((address_space(3))) void *)(tile + (k * 256 + wave * 64) * 16), 16,
+                                         0, 0);
 }
 // wait for this wave's outstanding loads (vmcnt 0), tile loads included
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
@@ -338,8 +343,7 @@ __device__ __forceinline__ void conv_slice(const bf16 *tile, const bf16x8 (&Wf)[
         bf16x8 A[6];
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
-            const int pix = (wave * RB + ir) * TXH + j + (k >> 1);
-            A[k] = *reinterpret_cast<const bf16x8 *>(tile + swz(pix, (k & 1) * 2 + kh) * 8);
+            A[k] = *reinterpret_cast<const bf16x8 *>(tile + tile_at(wave * RB + ir, j + (k >> 1), (k & 1) * 2 + kh) * 8);
         }
 #pragma unroll
         for (int k = 0; k < 6; ++k)
@@ -349,55 +353,63 @@ __device__ __forceinline__ void conv_slice(const bf16 *tile, const bf16x8 (&Wf)[
                 if (i >= 0 && i < RB)
                     acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Wf[dy * 6 + k], A[k], acc[i], 0, 0, 0);
             }
+        __builtin_amdgcn_sched_barrier(0);  // all rows' reads at the front would not fit the registers
     }
 }
 
-// A lane's outputs: point x, output channels 8 g + 4 kh .. + 3, rows y0 ..
-// y0 + RB - 1 of plane pz.  The half-waves exchange half of their channels
-// (v_permlane32_swap), so that a lane stores 16 channels as two 16-byte pieces
-// (lower half channels 0 - 15, upper half 16 - 31) and not four of 8 bytes.
+// A lane's outputs of a row: point x, output channels 8 g + 4 kh .. + 3.  The
+// half-waves exchange half of their channels (v_permlane32_swap), so that a
+// lane stores 16 channels as two 16-byte pieces (lower half channels 0 - 15,
+// upper half 16 - 31) and not four of 8 bytes.
+struct alignas(16) Packed {
+    uint32_t q[8];
+};
 template <int MODE>
-__device__ __forceinline__ void conv_store(const f32x16 (&acc)[RB], const f32x16 &bv, const bf16 *mask, bf16 *out,
-                                           int64_t pz, int y0, int x, int H, int W, int kh) {
+__device__ __forceinline__ Packed conv_pack(const f32x16 &acc, const f32x16 &bv) {
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    uint32_t p[4][2];  // [g][channel pair]
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            float a = acc[4 * g + 2 * k], b = acc[4 * g + 2 * k + 1];
+            if constexpr (MODE == kFwd) {
+                a = fmaxf(a + bv[4 * g + 2 * k], 0.0f);
+                b = fmaxf(b + bv[4 * g + 2 * k + 1], 0.0f);
+            }
+            const bf16x2 o = {(bf16)a, (bf16)b};
+            p[g][k] = __builtin_bit_cast(uint32_t, o);
+        }
+    Packed r;
+#pragma unroll
+    for (int g = 0; g < 2; ++g)  // lower half: channels 8 g .. 8 g + 7; upper half: 16 + 8 g ..
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const u32x2 x = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(p[g][k], p[g + 2][k], false, false));
+            r.q[4 * g + k] = x[0];
+            r.q[4 * g + 2 + k] = x[1];
+        }
+    return r;
+}
+// rows y0 .. y0 + RB - 1 of plane pz
+template <int MODE>
+__device__ __forceinline__ void conv_store(Packed (&v)[RB], const bf16 *mask, bf16 *out, int64_t pz, int y0, int x,
+                                           int H, int W, int kh) {
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
-        uint32_t p[4][2];  // [g][channel pair]
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                float a = acc[i][4 * g + 2 * k], b = acc[i][4 * g + 2 * k + 1];
-                if constexpr (MODE == kFwd) {
-                    a = fmaxf(a + bv[4 * g + 2 * k], 0.0f);
-                    b = fmaxf(b + bv[4 * g + 2 * k + 1], 0.0f);
-                }
-                const bf16x2 o = {(bf16)a, (bf16)b};
-                p[g][k] = __builtin_bit_cast(uint32_t, o);
-            }
-        alignas(16) uint32_t q[8];
-#pragma unroll
-        for (int g = 0; g < 2; ++g)  // lower half: channels 8 g .. 8 g + 7; upper half: 16 + 8 g ..
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const u32x2 r = __builtin_bit_cast(
-                    u32x2, __builtin_amdgcn_permlane32_swap(p[g][k], p[g + 2][k], false, false));
-                q[4 * g + k] = r[0];
-                q[4 * g + 2 + k] = r[1];
-            }
         const int y = y0 + i;
         if (y >= H || x >= W) continue;
         const int64_t idx = ((pz * H + y) * (int64_t)W + x) * C + 16 * kh;
         if constexpr (MODE == kBwd) {
             alignas(16) bf16 m[16];
-            bf16 *o = reinterpret_cast<bf16 *>(q);
+            bf16 *o = reinterpret_cast<bf16 *>(v[i].q);
             *reinterpret_cast<uint4 *>(m) = *reinterpret_cast<const uint4 *>(mask + idx);
             *reinterpret_cast<uint4 *>(m + 8) = *reinterpret_cast<const uint4 *>(mask + idx + 8);
 #pragma unroll
             for (int k = 0; k < 16; ++k) o[k] = (float)m[k] > 0.0f ? o[k] : (bf16)0.0f;
         }
-        *reinterpret_cast<uint4 *>(out + idx) = *reinterpret_cast<const uint4 *>(q);
-        *reinterpret_cast<uint4 *>(out + idx + 8) = *reinterpret_cast<const uint4 *>(q + 4);
+        *reinterpret_cast<uint4 *>(out + idx) = *reinterpret_cast<const uint4 *>(v[i].q);
+        *reinterpret_cast<uint4 *>(out + idx + 8) = *reinterpret_cast<const uint4 *>(v[i].q + 4);
     }
 }
 
@@ -425,7 +437,8 @@ __global__ __launch_bounds__(256, 3) void k_conv_mid(const bf16 *in, const bf16 
     const int64_t pz = blk / ((int64_t)tiles_x * tiles_y);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int j = lane & 31, kh = lane >> 5;
-    stage_tile(in + pz * H * W * C, conv_tile, x0, y0, H, W, wave, lane);
+#pragma unroll 1
+    for (int k = 0; k < CPL; ++k) stage_piece(in + pz * H * W * C, conv_tile, k, tile_piece(k, x0, y0, H, W), wave);
     bf16x8 Wf[K / 16];
 #pragma unroll
     for (int ks = 0; ks < K / 16; ++ks) Wf[ks] = *reinterpret_cast<const bf16x8 *>(wmat + j * K + ks * 16 + kh * 8);
@@ -435,7 +448,11 @@ __global__ __launch_bounds__(256, 3) void k_conv_mid(const bf16 *in, const bf16 
     wait_loads();
     __syncthreads();
     conv_slice(reinterpret_cast<const bf16 *>(conv_tile), Wf, acc, wave, j, kh);
-    conv_store<MODE>(acc, conv_bias<MODE>(bias, kh), mask, out, pz, y0 + wave * RB, x0 + j, H, W, kh);
+    const f32x16 bv = conv_bias<MODE>(bias, kh);
+    Packed v[RB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i) v[i] = conv_pack<MODE>(acc[i], bv);
+    conv_store<MODE>(v, mask, out, pz, y0 + wave * RB, x0 + j, H, W, kh);
 }
 
 // 3D: a workgroup marches along z through a run of planes.  Four plane tiles
@@ -443,11 +460,15 @@ __global__ __launch_bounds__(256, 3) void k_conv_mid(const bf16 *in, const bf16 
 // output plane needs and the next one, in flight while the products run, so an
 // activation is loaded once per run and not once per plane that needs it.
 // With a whole SIMD's registers a wave keeps the weights of all 27 taps (216
-// registers) for the whole run.  Bound by the matrix cores (216 products of
-// 32 clocks per wave and plane, against 1700 clocks of LDS reads per CU).
-// All three planes' tiles in LDS per output plane, the weights loaded per
-// plane and every operand read from LDS for each output row took 1387 us for
-// 4 x 128^3; this takes 507 us.
+// registers) for the whole run.  One wave per SIMD has no other to hide its
+// waits: each input row's operands are read during the products of the row
+// before, an output row is packed during the products after its last, and
+// the scheduler is kept from moving reads back to their use (it did, to save
+// registers: 500 us).  Bound by the matrix cores (216 products of 32 clocks
+// per wave and plane; 4 x 128^3 in 402 us are 1150 TFLOP/s, about what a large
+// bf16 matrix product reaches on this card).  All three planes' tiles in LDS
+// per output plane, the weights loaded per plane and every operand read from
+// LDS for each output row took 1387 us.
 template <int MODE>
 __global__ __launch_bounds__(256, 1) void k_conv_mid3(const bf16 *in, const bf16 *slices, const float *bias,
                                                       const bf16 *mask, bf16 *out, int H, int W, int nz, int tiles_x,
@@ -463,9 +484,13 @@ __global__ __launch_bounds__(256, 1) void k_conv_mid3(const bf16 *in, const bf16
     const int j = lane & 31, kh = lane >> 5;
     constexpr size_t TB = kConvLds;
     // plane z (periodic) into ring slot (z - zlo + 1) mod 4
+    uint32_t piece[CPL];
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) piece[k] = tile_piece(k, x0, y0, H, W);
     auto stage = [&](int z) {
-        stage_tile(in + (p0 + wrap(z, nz)) * HW * C, conv_tile + (size_t)((z - zlo + 1) & 3) * TB, x0, y0, H, W,
-                        wave, lane);
+        const bf16 *plane = in + (p0 + wrap(z, nz)) * HW * C;
+#pragma unroll
+        for (int k = 0; k < CPL; ++k) stage_piece(plane, conv_tile + (size_t)((z - zlo + 1) & 3) * TB, k, piece[k], wave);
     };
     stage(zlo - 1);
     stage(zlo);
@@ -477,19 +502,50 @@ __global__ __launch_bounds__(256, 1) void k_conv_mid3(const bf16 *in, const bf16
         for (int ks = 0; ks < K / 16; ++ks)
             Wf[d][ks] = *reinterpret_cast<const bf16x8 *>(slices + (size_t)d * C * K9 + j * K + ks * 16 + kh * 8);
     const f32x16 bv = conv_bias<MODE>(bias, kh);
+    int a6[6];  // this lane's six operands of a row, in the wave's first
+#pragma unroll
+    for (int k = 0; k < 6; ++k) a6[k] = tile_at(wave * RB, j + (k >> 1), (k & 1) * 2 + kh) * 8;
     wait_loads();
     for (int z = zlo; z < zhi; ++z) {
         lds_barrier();  // every wave's share of plane z + 1 is in LDS, and plane z - 2 has been read by all
         if (z + 2 <= zhi) stage(z + 2);
         f32x16 acc[RB];
+        Packed v[RB];
 #pragma unroll
         for (int i = 0; i < RB; ++i) acc[i] = f32x16{};
+        constexpr int NR = RB + 2, NG = 3 * NR;
+        const bf16 *slot[3];
 #pragma unroll
-        for (int d = 0; d < 3; ++d)
-            conv_slice(reinterpret_cast<const bf16 *>(conv_tile + (size_t)((z - zlo + d) & 3) * TB), Wf[d], acc,
-                            wave, j, kh);
+        for (int d = 0; d < 3; ++d) slot[d] = reinterpret_cast<const bf16 *>(conv_tile + (size_t)((z - zlo + d) & 3) * TB);
+        auto row = [&](int g, bf16x8 (&A)[6]) {  // input row g % NR of slice g / NR
+            const bf16 *tile = slot[g / NR];
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                A[k] = *reinterpret_cast<const bf16x8 *>(tile + a6[k] + (g % NR) * TXH * C);
+            }
+        };
+        bf16x8 A[2][6];
+        row(0, A[0]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            if (g + 1 < NG) row(g + 1, A[(g + 1) & 1]);
+#pragma unroll
+            for (int k = 0; k < 6; ++k)
+#pragma unroll
+                for (int dy = 0; dy < 3; ++dy) {
+                    const int i = g % NR - dy;
+                    if (i >= 0 && i < RB)
+                        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Wf[g / NR][dy * 6 + k], A[g & 1][k], acc[i], 0,
+                                                                        0, 0);
+                }
+            // a row's sums are complete after its last input row: packed during the next products
+            if (g > NG - RB) v[g - 1 - (NG - RB)] = conv_pack<MODE>(acc[g - 1 - (NG - RB)], bv);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        v[RB - 1] = conv_pack<MODE>(acc[RB - 1], bv);
         wait_loads();  // plane z + 2, before the stores: they need not be waited for
-        conv_store<MODE>(acc, bv, mask, out, p0 + z, y0 + wave * RB, x0 + j, H, W, kh);
+        conv_store<MODE>(v, mask, out, p0 + z, y0 + wave * RB, x0 + j, H, W, kh);
     }
 }
 
