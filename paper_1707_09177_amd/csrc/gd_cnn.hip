@@ -50,7 +50,10 @@ namespace gdcnn {
 typedef __bf16 bf16;
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int C = 32;           // channels
 constexpr int K9 = 9 * C;       // reduction length of one 3x3 slice
@@ -58,7 +61,6 @@ constexpr int NL = 6;           // layers
 constexpr int K = K9;           // reduction length of a 2D 32 -> 32 layer (one MFMA pass)
 constexpr int NMID = NL - 2;    // 32 -> 32 layers
 constexpr int TX = 32;          // columns of a conv tile or a weight-gradient strip (one MFMA tile)
-constexpr int PSTR = 40;        // LDS stride of one point in the fused forward's rings (32 channels + 8 pad) in bf16
 constexpr int NW_MID = C * K + C;  // weights + biases of a 32 -> 32 layer
 constexpr int NW_END = K + C;      // either end layer's weights (288) + up to 32 biases
 constexpr int RMS_CHUNKS = 64;
@@ -288,7 +290,7 @@ __global__ __launch_bounds__(256) void k_conv_end(const T *in, const double *s, 
 // operands: three taps, two channel halves) and used for the three output
 // rows it belongs to, with the weights in registers.  Products per output run
 // dz, dy, dx, channel half in order.
-constexpr int kFwd = 0, kBwd = 1;
+constexpr int kFwd = 0, kBwd = 1, kFused = 2;  // kFused: the bias is in the sums already
 constexpr int TXH = TX + 2;  // tile columns with the halo
 constexpr int RB = 4;        // output rows per wave (8 in 2D measured the same)
 constexpr size_t kConvLds = (size_t)(4 * RB + 2) * TXH * C * sizeof(bf16);  // one plane's tile
@@ -357,6 +359,12 @@ __device__ __forceinline__ void conv_slice(const bf16 *tile, const bf16x8 (&Wf)[
     }
 }
 
+// max(x, 0) as one integer max on the bits (a negative float is a negative
+// integer): fmaxf also quiets signalling NaNs, one more instruction per value
+__device__ __forceinline__ float relu_bits(float x) {
+    return __builtin_bit_cast(float, max(__builtin_bit_cast(int, x), 0));
+}
+
 // A lane's outputs of a row: point x, output channels 8 g + 4 kh .. + 3.  The
 // half-waves exchange half of their channels (v_permlane32_swap), so that a
 // lane stores 16 channels as two 16-byte pieces (lower half channels 0 - 15,
@@ -366,7 +374,6 @@ struct alignas(16) Packed {
 };
 template <int MODE>
 __device__ __forceinline__ Packed conv_pack(const f32x16 &acc, const f32x16 &bv) {
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     uint32_t p[4][2];  // [g][channel pair]
 #pragma unroll
     for (int g = 0; g < 4; ++g)
@@ -376,6 +383,9 @@ __device__ __forceinline__ Packed conv_pack(const f32x16 &acc, const f32x16 &bv)
             if constexpr (MODE == kFwd) {
                 a = fmaxf(a + bv[4 * g + 2 * k], 0.0f);
                 b = fmaxf(b + bv[4 * g + 2 * k + 1], 0.0f);
+            } else if constexpr (MODE == kFused) {
+                a = relu_bits(a);
+                b = relu_bits(b);
             }
             const bf16x2 o = {(bf16)a, (bf16)b};
             p[g][k] = __builtin_bit_cast(uint32_t, o);
@@ -553,45 +563,54 @@ __global__ __launch_bounds__(256, 1) void k_conv_mid3(const bf16 *in, const bf16
 //
 // Inference in 2D runs all six layers in one kernel, so no activation goes
 // through HBM.  A workgroup owns a strip of FV output columns and up to FY
-// rows of one sample and marches down it.  Layer l keeps the rows of its
-// input that its 3x3 taps need in an LDS ring (layers 2 .. 6; layer 1 reads
-// ubar / s from a ring of its own); at step s layer l computes row
-// ys + s - 2 (l - 1), two rows behind layer l - 1, so every input row a layer
-// reads was written in an earlier step, and the row it writes goes to the
-// fourth ring slot, which no layer reads in that step: one barrier per step.
+// rows of one sample and marches down it, two rows of every layer per step.
+// Layer l keeps the rows of its input that its 3x3 taps need in an LDS ring
+// (layers 2 .. 6; layer 1 reads ubar / s from a ring of its own); at step s
+// layer l computes rows ys + 2 s - 3 (l - 1) and the next, three rows behind
+// layer l - 1: the four input rows it reads were written in the two steps
+// before, and the two it writes go to slots that no layer reads in that step,
+// so a ring has six slots and a step one barrier.  The slots depend on s mod 3
+// alone: the step loop is unrolled by three, and every LDS address is a
+// register set up once plus a constant.  A layer outside its rows computes on
+// stale ring rows; what it writes reaches no row that is needed.
 // Columns: a frame of FW = 64 columns starting 5 left of the strip.  Layer l's
 // row is needed on frame columns l - 1 .. FV + 10 - l, so with FV = 54 every
 // layer computes the frame's 64 columns (two MFMA tiles for the 32 -> 32
 // layers, one column per lane for layer 1) and layer 6 the strip's 54.
-// A wave's work in a step has no branch (a layer outside its rows computes
-// on stale ring rows and does not write), so the scheduler can interleave
-// the matrix products with the vector work of layers 1 and 6.
+// Layers 1 and 6 run on the matrix cores too: layer 1 on values of ubar / s
+// split into three bf16 terms (exact, so its products are those of FP32
+// inputs), layer 6 as the products of an input column with all nine taps, which
+// the next step sums.  Each took as many vector instructions as there are
+// clocks of matrix products.
+// Bound by the matrix cores (38.5 products of 32 clocks per wave and step, two
+// waves per SIMD: two thirds of the time) and a step's latency.  16 x 1024^2:
+// one row per step, with layers 1 and 6 on the vector units, 1824 us; two rows
+// per step 1571; this 1300 (950 TFLOP/s of the 32 -> 32 layers alone).
 constexpr int FW = 64, FV = FW - 10, FY = 256, FRC = FW + 2;  // frame, strip, rows per workgroup, ring columns
 constexpr int FTHREADS = 512;
-constexpr int RSL = 4;        // ring slots: three rows read, the fourth written in the same step
-constexpr int RTR = RSL;      // a fifth slot per ring takes the rows of layers outside their rows
+constexpr int RSL = 6;        // ring slots: four rows read, two written in the same step
+constexpr int RROW = FRC * C; // elements of a ring row
 constexpr int URC = FRC;      // ubar ring columns: frame -1 .. FW
-constexpr int URS = 64;       // ubar ring rows
-constexpr int UBATCH = 16;    // ubar rows loaded together, every UBATCH steps
-constexpr size_t kRingBytes = (size_t)(NL - 1) * (RSL + 1) * FRC * PSTR * sizeof(bf16);
-constexpr size_t kFusedLds = kRingBytes + URS * URC * sizeof(float) + 2 * 8 * 64 * sizeof(float);
+constexpr int URS = 32;       // ubar ring rows
+constexpr int UBATCH = 6;     // ubar rows loaded together, every three steps
+static_assert(UBATCH * FRC <= FTHREADS, "one ubar value per thread");
+constexpr size_t kRingBytes = (size_t)(NL - 1) * RSL * RROW * sizeof(bf16);
+constexpr size_t kURingBytes = (size_t)URS * URC * sizeof(u32x2);
+constexpr size_t kFusedLds = kRingBytes + kURingBytes + (size_t)RSL * 3 * FW * sizeof(f32x4);
 static_assert(kFusedLds <= 160 * 1024, "LDS of one CU");
-
-// max(x, 0) as one integer max on the bits (a negative float is a negative
-// integer): fmaxf also quiets signalling NaNs, one more instruction per value
-__device__ __forceinline__ float relu_bits(float x) {
-    return __builtin_bit_cast(float, max(__builtin_bit_cast(int, x), 0));
-}
 
 template <typename T>
 __global__ __launch_bounds__(FTHREADS) void k_fwd2d_fused(const T *ub, const double *s, const bf16 *wbf,
                                                           const float *params, Offsets off, float *z, int H, int W) {
     extern __shared__ __attribute__((aligned(16))) unsigned char fused_lds[];
-    bf16 *ring = reinterpret_cast<bf16 *>(fused_lds);                  // [layer 2..6][slot RSL][FRC][PSTR]
-    float *uring = reinterpret_cast<float *>(fused_lds + kRingBytes);  // ubar / s: [row slot URS][URC]
-    float *zpart = uring + URS * URC;  // layer 6 partial sums [step parity][wave][column]
-    auto at = [&](int l, int slot, int col) { return ring + (((l - 2) * (RSL + 1) + slot) * FRC + col) * PSTR; };
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    bf16 *ring = reinterpret_cast<bf16 *>(fused_lds);                  // [layer 2..6][slot RSL][FRC][C]
+    u32x2 *uring = reinterpret_cast<u32x2 *>(fused_lds + kRingBytes);  // ubar / s: [row slot URS][URC]
+    // layer 6's products: [slot RSL][taps 4 t .. 4 t + 3][frame column]
+    f32x4 *zring = reinterpret_cast<f32x4 *>(fused_lds + kRingBytes + kURingBytes);
+    // channels 8 c .. 8 c + 7 of a ring column, in slot 0 of layer l's input;
+    // a column's four chunks are permuted by its index
+    auto at = [&](int l, int col, int c) { return ring + (l - 2) * RSL * RROW + col * C + (c ^ ((col >> 2) & 3)) * 8; };
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = blockIdx.z;
     const int x0 = blockIdx.x * FV, y0 = blockIdx.y * FY;
     const int rows = min(FY, H - y0);
@@ -615,145 +634,153 @@ __global__ __launch_bounds__(FTHREADS) void k_fwd2d_fused(const T *ub, const dou
     f32x16 mb;  // biases of the output channels this lane holds: the accumulator's start
 #pragma unroll
     for (int v = 0; v < 16; ++v) mb[v] = params[off.b[ML - 1] + 8 * (v >> 2) + 4 * kh + (v & 3)];
-    // layers 1 and 6: wave w takes channels 4w .. 4w + 3, so their weights are
-    // uniform across the wave
-    const int q = __builtin_amdgcn_readfirstlane(wave);
-    float w1r[4][9], b1r[4];
-    bf16x2 w6p[9][2];
+    // layers 1 and 6: wave w takes frame columns 16 (w % 4) .. of the step's
+    // first (w < 4) or second row, lane group g = lane / 16 a quarter of the
+    // reduction.  Layer 1's has the slots 4 t .. 4 t + 2 for the three terms of
+    // tap t < 8, and slots 3, 7 and 11 for those of tap 8.
+    const int orow = wave >> 2, pcol = 16 * (wave & 3) + (lane & 15), g4 = lane >> 4;
+    bf16x8 W1f[2], W6f;
+    f32x4 b1[2];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        b1r[k] = params[off.b[0] + 4 * q + k];
+    for (int h = 0; h < 2; ++h) {
+        const int ch = 16 * h + (lane & 15);
 #pragma unroll
-        for (int t = 0; t < 9; ++t) w1r[k][t] = (float)wbf[off.W[0] + (4 * q + k) * 9 + t];
+        for (int e = 0; e < 8; ++e) {
+            const int k = 8 * g4 + e, t = (k & 3) < 3 ? k >> 2 : (k < 12 ? 8 : -1);
+            W1f[h][e] = t >= 0 ? wbf[off.W[0] + ch * 9 + t] : (bf16)0.0f;
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) b1[h][v] = params[off.b[0] + 16 * h + 4 * g4 + v];
     }
 #pragma unroll
-    for (int t = 0; t < 9; ++t)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) w6p[t][h] = *reinterpret_cast<const bf16x2 *>(wbf + off.W[NL - 1] + t * C + 4 * q + 2 * h);
+    for (int e = 0; e < 8; ++e)
+        W6f[e] = (lane & 15) < 9 ? wbf[off.W[NL - 1] + (lane & 15) * C + 8 * g4 + e] : (bf16)0.0f;
     const float b6 = params[off.b[NL - 1]];
 
-    // ubar / s enters a ring of URS rows (row ys - 1 + rho in slot rho % URS)
-    // in batches of UBATCH rows, loaded a whole batch ahead: the loads of a
-    // batch are waited for once, not once per step
+    // ubar / s enters a ring of URS rows (row ys - 1 + rho in slot rho % URS),
+    // six rows per three steps and one value per thread: loaded three steps
+    // before they are stored, and stored before the steps that read them
+    const int ur = tid / URC, uc = tid - ur * URC;
+    const int64_t ux = ((x0 - 6 + uc) % W + W) % W;
     const int nu = rows + 12;  // rows rho = 0 .. rows + 11 feed layer 1
-    auto urow = [&](int rho) { return (int64_t)((((ys - 1 + rho) % H) + H) % H) * W; };
-    constexpr int UPT = (UBATCH * URC + FTHREADS - 1) / FTHREADS;  // loads per thread per batch
-    T ubuf[UPT];
-    auto ubatch_load = [&](int rho0) {  // rows rho0 .. rho0 + UBATCH - 1
-#pragma unroll
-        for (int k = 0; k < UPT; ++k) {
-            const int e = tid + FTHREADS * k, rho = rho0 + e / URC, col = e % URC;
-            ubuf[k] = (e < UBATCH * URC && rho < nu) ? ubs[urow(rho) + ((x0 - 6 + col) % W + W) % W] : T(0);
+    auto u_load = [&](int rho0) {
+        const int rho = rho0 + ur;
+        return ur < UBATCH && rho < nu ? (float)ubs[(int64_t)((((ys - 1 + rho) % H) + H) % H) * W + ux] * inv : 0.0f;
+    };
+    // as the sum of three bf16 terms of 8 bits each, exact for the 24 bits of v
+    auto u_store = [&](int rho0, float v) {
+        if (ur < UBATCH) {
+            const bf16 hi = (bf16)v, mid = (bf16)(v - (float)hi), lo = (bf16)(v - (float)hi - (float)mid);
+            const bf16x2 a = {hi, mid}, b = {lo, (bf16)0.0f};
+            uring[((rho0 + ur) & (URS - 1)) * URC + uc] = {__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b)};
         }
     };
-    auto ubatch_store = [&](int rho0) {
-#pragma unroll
-        for (int k = 0; k < UPT; ++k) {
-            const int e = tid + FTHREADS * k, rho = rho0 + e / URC, col = e % URC;
-            if (e < UBATCH * URC && rho < nu) uring[(rho % URS) * URC + col] = (float)ubuf[k] * inv;
-        }
-    };
-    ubatch_load(0);
-    ubatch_store(0);
-    ubatch_load(UBATCH);
-    ubatch_store(UBATCH);
+    u_store(0, u_load(0));
+    u_store(UBATCH, u_load(UBATCH));
+    float unext = u_load(2 * UBATCH);
     __syncthreads();
 
-    const int nstep = rows + 15;  // layer 6 computes rows y0 .. y0 + rows - 1 at steps 15 .. rows + 14
-    const int l6c = min(lane, FV - 1);  // layer 6: output frame column 5 + l6c
-    // z of layer 6's row at step st2: the 8 waves' partial sums, in wave order
-    auto zsum_out = [&](int st2) {
-        if (st2 >= 15 && tid < FV) {
-            const float *zp = zpart + (st2 & 1) * 8 * 64;
-            float zsum = b6;
+    const int nstep = 11 + (rows + 1) / 2;  // z of rows y0 .. from step 11 on
+    // this lane's places in the rings, in slot 0
+    const bf16 *am[6];  // layer ML's operands of an input row: taps k / 2, channel halves k % 2
 #pragma unroll
-            for (int w = 0; w < 8; ++w) zsum += zp[w * 64 + tid];
-            const int x = x0 + tid;
-            if (x < W) z[(int64_t)b * HW + (int64_t)(ys + st2 - 10) * W + x] = zsum;
-        }
+    for (int k = 0; k < 6; ++k) am[k] = at(ML, 32 * mh + j + (k >> 1), (k & 1) * 2 + kh);
+    const bf16 *a6 = at(NL, pcol + 1, g4);  // layer 6's input
+    f32x4 *z6 = zring + g4 * FW + pcol;     // and products
+    bf16 *wm[2];  // layer ML's outputs, 16 channels per lane
+#pragma unroll
+    for (int g = 0; g < 2; ++g) wm[g] = at(ML + 1, 32 * mh + j + 1, 2 * kh + g);
+    bf16 *w1[2];  // layer 1's, 4 channels per lane and half
+#pragma unroll
+    for (int h = 0; h < 2; ++h) w1[h] = at(2, pcol + 1, 2 * h + (g4 >> 1)) + (g4 & 1) * 4;
+    // layer 1's operands: taps 2 g and 2 g + 1, and tap 8's terms for the free slots
+    const int t0 = 2 * g4, t1 = t0 + 1;
+    const uint32_t keep_x = g4 < 2 ? ~0u : 0u, keep_y = g4 == 0 ? 0xffff0000u : 0u;
+    auto row = [&](int slot, bf16x8 (&A)[6]) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) A[k] = *reinterpret_cast<const bf16x8 *>(am[k] + slot * RROW);
     };
-    for (int st = 0; st < nstep; ++st) {
-        // ubar rows 2 UBATCH + st .. are loaded at the start of the step and
-        // stored at its end (layer 1 reads rows st .. st + 2 of the ring)
-        const bool ub_now = st % UBATCH == 0 && 2 * UBATCH + st < nu;
-        if (ub_now) ubatch_load(2 * UBATCH + st);
-        const int yM = ys + st - 2 * (ML - 1);
-        const bool mact = st >= 3 * ML - 3 && st < 3 * ML - 3 + rows + 2 * (NL - ML);
-        // ---- operand loads: layer ML's 18 fragments, layer 1's 9 ubar values,
-        // layer 6's 9 channel quads.  Slots are row & (RSL - 1), also for the
-        // (negative) rows of a layer before its first step; per input row one
-        // base address, the taps' column offsets are immediates.
-        const int rM = yM - 1 - ys;  // relative index of layer ML's first input row
-        bf16x8 Af[K / 16];
-#pragma unroll
-        for (int dy = 0; dy < 3; ++dy) {
-            const bf16 *rb = at(ML, (rM + dy) & (RSL - 1), 32 * mh + j) + kh * 8;
-#pragma unroll
-            for (int k = 0; k < 6; ++k)  // taps (dy, dx = k / 2), channel halves k % 2
-                Af[6 * dy + k] = *reinterpret_cast<const bf16x8 *>(rb + (k >> 1) * PSTR + (k & 1) * 16);
-        }
-        float xv[9];
-#pragma unroll
-        for (int dy = 0; dy < 3; ++dy) {  // ubar row ys + st + dy - 1 is rho = st + dy; frame column lane + dx - 1
-            const float *ur = uring + ((st + dy) & (URS - 1)) * URC + lane;
-#pragma unroll
-            for (int dx = 0; dx < 3; ++dx) xv[3 * dy + dx] = ur[dx];
-        }
-        bf16x2 a6[9][2];
-#pragma unroll
-        for (int dy = 0; dy < 3; ++dy) {  // layer 6 reads rows ys + st - 11 .. ys + st - 9
-            const bf16 *rb = at(NL, (st - 11 + dy) & (RSL - 1), 5 + l6c) + 4 * q;  // frame column 5 + l6c + dx - 1
-#pragma unroll
-            for (int dx = 0; dx < 3; ++dx) {
-                a6[3 * dy + dx][0] = *reinterpret_cast<const bf16x2 *>(rb + dx * PSTR);
-                a6[3 * dy + dx][1] = *reinterpret_cast<const bf16x2 *>(rb + dx * PSTR + 2);
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);  // every load above is issued before the first product
-        // ---- products
-        f32x16 acc = mb;
-#pragma unroll
-        for (int ks = 0; ks < K / 16; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Wf[ks], Af[ks], acc, 0, 0, 0);
-        alignas(8) bf16 v1[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            float a = b1r[k];
-#pragma unroll
-            for (int t = 0; t < 9; ++t) a += w1r[k][t] * xv[t];
-            v1[k] = (bf16)relu_bits(a);
-        }
-        float zp = 0.0f;
-#pragma unroll
-        for (int t = 0; t < 9; ++t)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) zp = __builtin_amdgcn_fdot2_f32_bf16(a6[t][h], w6p[t][h], zp, false);
-        // interleave: one matrix product, then a share of the vector work
-#pragma unroll
-        for (int i = 0; i < K / 16; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-            __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);  // VALU
-        }
+    // a step's first two input rows are older than the step before and are
+    // read ahead of its barrier
+    bf16x8 A[2][6];
+    row(2, A[0]);
+    row(3, A[1]);
+    auto step = [&](auto phase, int st) {
+        constexpr int c = phase.value;
+        constexpr int in_slot[4] = {2 * ((c + 1) % 3), 2 * ((c + 1) % 3) + 1, 2 * ((c + 2) % 3), 2 * ((c + 2) % 3) + 1};
+        auto uval = [&](int t) {  // ubar row ys + 2 st + orow + t / 3 - 1, frame column pcol + t % 3 - 1
+            return uring + ((2 * st + orow + t / 3) & (URS - 1)) * URC + pcol + t % 3;
+        };
+        const u32x2 ua = *uval(t0), ub1 = *uval(t1);
+        const uint32_t u8 = reinterpret_cast<const uint32_t *>(uval(8))[g4 == 0 ? 0 : 1];
+        const bf16x8 A6 = *reinterpret_cast<const bf16x8 *>(a6 + (orow ? in_slot[3] : in_slot[2]) * RROW);
         __builtin_amdgcn_sched_barrier(0);
-        // ---- writes: rows for the next steps' readers, into this step's free
-        // slots (a layer outside its rows writes to the spare slot: no branch)
-        {
-            bf16 *dst = at(ML + 1, mact ? (yM - ys) & (RSL - 1) : RTR, 32 * mh + j + 1);
+        f32x16 acc[2] = {mb, mb};
+        // the products of input row g, per output row and tap in order
+        auto products = [&](int g) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                alignas(8) bf16 v4[4];
+            for (int k = 0; k < 6; ++k)
 #pragma unroll
-                for (int k = 0; k < 4; ++k) v4[k] = (bf16)relu_bits(acc[4 * g + k]);
-                *reinterpret_cast<uint2 *>(dst + 8 * g + 4 * kh) = *reinterpret_cast<const uint2 *>(v4);
+                for (int o = 0; o < 2; ++o) {
+                    const int dy = g - o;
+                    if (dy >= 0 && dy < 3)
+                        acc[o] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Wf[dy * 6 + k], A[g & 1][k], acc[o], 0, 0, 0);
+                }
+        };
+        auto layer1 = [&]() {
+            const u32x4 x = {ua[0], ua[1] | (u8 & keep_x) << 16, ub1[0], ub1[1] | (u8 & keep_y)};
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const f32x4 d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W1f[h], __builtin_bit_cast(bf16x8, x), b1[h], 0, 0, 0);
+                alignas(8) bf16 v[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[k] = (bf16)relu_bits(d[k]);
+                *reinterpret_cast<uint2 *>(w1[h] + (orow ? 2 * c + 1 : 2 * c) * RROW) = *reinterpret_cast<const uint2 *>(v);
             }
+        };
+        auto write = [&](int o) {
+            const Packed v = conv_pack<kFused>(acc[o], mb);
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+                *reinterpret_cast<uint4 *>(wm[g] + (2 * c + o) * RROW) = *reinterpret_cast<const uint4 *>(v.q + 4 * g);
+        };
+        products(0);
+        layer1();
+        __builtin_amdgcn_sched_barrier(0);
+        row(in_slot[2], A[0]);
+        products(1);
+        const f32x4 d6 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W6f, A6, f32x4{}, 0, 0, 0);
+        if (g4 < 3) z6[(orow ? 2 * c + 1 : 2 * c) * 3 * FW] = d6;
+        __builtin_amdgcn_sched_barrier(0);
+        row(in_slot[3], A[1]);
+        products(2);
+        __builtin_amdgcn_sched_barrier(0);
+        row(in_slot[2], A[0]);  // the next step's first
+        products(3);
+        write(0);
+        __builtin_amdgcn_sched_barrier(0);
+        row(in_slot[3], A[1]);
+        write(1);
+        // z of rows y0 + 2 st - 22 and the next: their input rows' products are
+        // those of the two steps before
+        if (wave < 2) {
+            const int y = 2 * (st - 11) + wave, x = x0 + lane;
+            float zs = b6;
+#pragma unroll
+            for (int t = 0; t < 9; ++t)
+                zs += zring[((wave ? in_slot[t / 3 + 1] : in_slot[t / 3]) * 3 + (t >> 2)) * FW + min(lane, FV - 1) + 4 + t % 3][t & 3];
+            if (st >= 11 && lane < FV && y < rows && x < W) z[(int64_t)b * HW + (int64_t)(y0 + y) * W + x] = zs;
         }
-        *reinterpret_cast<uint2 *>(at(2, st < rows + 10 ? st & (RSL - 1) : RTR, lane + 1) + 4 * q) =
-            *reinterpret_cast<const uint2 *>(v1);  // layer 1: frame column lane
-        zpart[(st & 1) * 8 * 64 + q * 64 + lane] = zp;
-        zsum_out(st - 1);  // the previous step's partial sums are complete (barrier below it)
-        if (ub_now) ubatch_store(2 * UBATCH + st);
         lds_barrier();
+    };
+    for (int st = 0; st < nstep; st += 3) {
+        // layer 1 reads rows 2 st .. 2 st + 9 in these three steps
+        u_store(2 * st + 2 * UBATCH, unext);
+        unext = u_load(2 * st + 3 * UBATCH);
+        step(std::integral_constant<int, 0>{}, st);
+        if (st + 1 < nstep) step(std::integral_constant<int, 1>{}, st + 1);
+        if (st + 2 < nstep) step(std::integral_constant<int, 2>{}, st + 2);
     }
-    zsum_out(nstep - 1);
 }
 
 // layer 6: 32 channels -> 1, no activation: z.  On the matrix cores: one

@@ -54,3 +54,14 @@ def test_gradients_and_forward(shape):
         n = W.size + b.size
         assert rel_l2(g[off:off + n], g_ref[off:off + n]) <= 2e-2, li
         off += n
+
+
+# the fused 2D forward marches two rows per step down strips of 54 columns and 256 rows
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("shape", [(1, 54), (2, 55), (3, 1), (6, 108), (255, 53), (256, 20), (257, 54), (258, 109), (515, 7)])
+def test_fused_forward_pairs_of_rows(shape, dtype):
+    p, ub, _ = inputs(shape, 2)
+    got = gdecon.WarmStart(p, band=None).forward(to_dev(ub, dtype)).double().cpu().numpy()
+    ref = cnn.forward(p, ub, emulate_bf16=True)
+    y = (got - ub) / ref["s"][:, None, None]
+    assert rel_l2(y, ref["y"]) <= 3e-3, rel_l2(y, ref["y"])
