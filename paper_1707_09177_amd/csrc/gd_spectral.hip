@@ -556,14 +556,54 @@ __device__ __forceinline__ double kpow_of(int64_t k2, double kpow, int ipow) {
     return ipow > 0 ? r : 1.0 / r;
 }
 
+// shell_of on the device: k2 <= 3 * 2048^2 < 2^24 is exact in FP32, and the
+// root's rounding is undone by the same integer tests
+__device__ __forceinline__ int shell_dev(int k2) {
+    int s = (int)__builtin_amdgcn_sqrtf((float)k2);
+    if ((2 * s + 1) * (2 * s + 1) <= 4 * k2) ++s;
+    if (s > 0 && (2 * s - 1) * (2 * s - 1) > 4 * k2) --s;
+    return s;
+}
+
+// Inclusive scan over the lanes of a wave within runs of equal keys, which
+// are nondecreasing: within rows of 16 lanes by DPP, then row after row from
+// the last lane of the row before (equal keys there mean that the run reaches
+// back to it).  Through the LDS crossbar the six steps were most of
+// k_spectrum_part's time.
+template <int CTRL>
+__device__ __forceinline__ void run_step(double &v, int key) {
+    const uint64_t x = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), CTRL, 0xf, 0xf, true);
+    const int ok = __builtin_amdgcn_update_dpp(-2, key, CTRL, 0xf, 0xf, false);  // -2 where the row has no such lane
+    if (ok == key) v += __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ void run_scan(double &v, int key, int lane) {
+    run_step<0x111>(v, key);  // row_shr 1, 2, 4, 8
+    run_step<0x112>(v, key);
+    run_step<0x114>(v, key);
+    run_step<0x118>(v, key);
+#pragma unroll
+    for (int r = 1; r < 4; ++r) {
+        const uint64_t x = __builtin_bit_cast(uint64_t, v);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, 16 * r - 1);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), 16 * r - 1);
+        const int ok = __builtin_amdgcn_readlane(key, 16 * r - 1);
+        if (lane >> 4 == r && ok == key) v += __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+    }
+}
+
 // Partial shell sums of one chunk of rows of one field's stored spectrum:
 // 1/2 w(k_x) |X / N|^2 |k|^p per coefficient, accumulated per shell in LDS.
 // A wave takes whole rows; along a row |k| grows with k_x, so the lanes of a
 // wave hold nondecreasing shells, summed by a segmented scan before one LDS
-// update per segment.  Every wave of the workgroup (blockDim.x / 64 of them)
-// has its own bins, which no other wave touches, and adds into them in
-// program order; the waves' bins are then summed in wave order.  So the
-// result does not depend on timing.
+// update per segment; the column k_x = n_x / 2, which would fill one lane of
+// another round, is added by lane 0.  Every wave of the workgroup
+// (blockDim.x / 64 of them) has its own bins, which no other wave touches,
+// and adds into them in program order; the waves' bins are then summed in
+// wave order.  So the result does not depend on timing.
+// Bound by the read of the spectrum: 3 x 256^3 FP64 218 us with the scan
+// through the LDS crossbar and 64-bit integer shells, 117 now.
 template <typename T>
 __global__ __launch_bounds__(256) void k_spectrum_part(const T *X, double *part, int64_t rows_per_field,
                                                        int64_t rows_per_chunk, int64_t nchunks, int64_t nshells, Spec s,
@@ -575,39 +615,42 @@ __global__ __launch_bounds__(256) void k_spectrum_part(const T *X, double *part,
     for (int64_t i = threadIdx.x; i < nwaves * nshells; i += blockDim.x) all_bins[i] = 0.0;
     __syncthreads();
     const int64_t b = blockIdx.x / nchunks, ch = blockIdx.x % nchunks;
-    const int64_t row0 = ch * rows_per_chunk, row1 = std::min(rows_per_field, row0 + rows_per_chunk);
+    const int row0 = (int)(ch * rows_per_chunk), row1 = (int)std::min(rows_per_field, ch * rows_per_chunk + rows_per_chunk);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int ny = (int)s.ny, nz = (int)s.nz, half = (int)(s.nx / 2);
     double *bins = all_bins + wave * nshells;
     const V *F = reinterpret_cast<const V *>(X) + b * rows_per_field * s.nxh;
     const double inv_n2 = 1.0 / ((double)(s.nx * s.ny * s.nz) * (double)(s.nx * s.ny * s.nz));
-    for (int64_t row = row0 + wave; row < row1; row += nwaves) {
-        const int64_t ky = row % s.ny, kz = row / s.ny;
-        const int64_t a = ky <= s.ny / 2 ? ky : ky - s.ny, c = kz <= s.nz / 2 ? kz : kz - s.nz;
-        const int64_t kyz2 = a * a + c * c;
-        for (int64_t kx0 = 0; kx0 < s.nxc; kx0 += 64) {
-            const int64_t kx = kx0 + lane;
-            double v = 0.0;
-            int64_t key = -1;
-            if (kx < s.nxc) {
-                const V z = F[row * s.nxh + kx];
-                const int64_t k2 = kx * kx + kyz2;
-                const double w = (kx == 0 || 2 * kx == s.nx) ? 0.5 : 1.0;
-                double kp = 1.0;
-                if (kpow != 0.0) kp = k2 > 0 ? kpow_of(k2, kpow, ipow) : 0.0;
-                v = w * ((double)z.x * (double)z.x + (double)z.y * (double)z.y) * inv_n2 * kp;
-                key = shell_of(k2);
-            }
-            // segmented inclusive scan over equal, contiguous keys
+    auto term = [&](V z, int k2, bool edge) {
+        double kp = 1.0;
+        if (kpow != 0.0) kp = k2 > 0 ? kpow_of(k2, kpow, ipow) : 0.0;
+        return (edge ? 0.5 : 1.0) * ((double)z.x * (double)z.x + (double)z.y * (double)z.y) * inv_n2 * kp;
+    };
+    for (int row = row0 + wave; row < row1; row += nwaves) {
+        const int ky = row & (ny - 1), kz = row / ny;  // ny is a power of two
+        const int a = ky <= ny / 2 ? ky : ky - ny, c = kz <= nz / 2 ? kz : kz - nz;
+        const int kyz2 = a * a + c * c;
+        const V *R = F + (int64_t)row * s.nxh;
+        const V last = R[half];
+        for (int kx0 = 0; kx0 < half; kx0 += 128) {
+            V z[2];
 #pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const double ov = __shfl_up(v, off, 64);
-                const int64_t ok = __shfl_up(key, off, 64);
-                if (lane >= off && ok == key) v += ov;
+            for (int k = 0; k < 2; ++k) z[k] = R[min(kx0 + 64 * k + lane, half)];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int kx = kx0 + 64 * k + lane;
+                if (kx0 + 64 * k >= half) break;
+                const int k2 = kx * kx + kyz2;
+                const int key = kx < half ? shell_dev(k2) : -1;
+                double v = kx < half ? term(z[k], k2, kx == 0) : 0.0;
+                run_scan(v, key, lane);
+                // one lane per segment: distinct bins within this update
+                const int next = __shfl_down(key, 1, 64);
+                if (key >= 0 && (lane == 63 || next != key)) bins[key] += v;
             }
-            // one lane per segment: distinct bins within this update
-            const int64_t next = __shfl_down(key, 1, 64);
-            if (key >= 0 && (lane == 63 || next != key)) bins[key] += v;
         }
+        const int k2 = half * half + kyz2;
+        if (lane == 0) bins[shell_dev(k2)] += term(last, k2, true);
     }
     __syncthreads();
     double *dst = part + (b * nchunks + ch) * nshells;
