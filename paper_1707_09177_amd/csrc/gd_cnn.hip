@@ -577,15 +577,14 @@ __global__ __launch_bounds__(256, 1) void k_conv_mid3(const bf16 *in, const bf16
 // row is needed on frame columns l - 1 .. FV + 10 - l, so with FV = 54 every
 // layer computes the frame's 64 columns (two MFMA tiles for the 32 -> 32
 // layers, one column per lane for layer 1) and layer 6 the strip's 54.
-// Layers 1 and 6 run on the matrix cores too: layer 1 on values of ubar / s
-// split into three bf16 terms (exact, so its products are those of FP32
-// inputs), layer 6 as the products of an input column with all nine taps, which
-// the next step sums.  Each took as many vector instructions as there are
-// clocks of matrix products.
-// Bound by the matrix cores (38.5 products of 32 clocks per wave and step, two
-// waves per SIMD: two thirds of the time) and a step's latency.  16 x 1024^2:
-// one row per step, with layers 1 and 6 on the vector units, 1824 us; two rows
-// per step 1571; this 1300 (950 TFLOP/s of the 32 -> 32 layers alone).
+// Layer 6 runs on the matrix cores too, as the products of an input column
+// with all nine taps, which the next step sums.  Layer 1 stays on the vector
+// units: as matrix products of exact bf16 terms of ubar / s it took 100 us
+// less, but another order of its sums flips bf16 roundings of its output.
+// Bound by the matrix cores (37 products of 32 clocks per wave and step, two
+// waves per SIMD: 60 % of the time) and a step's latency.  16 x 1024^2: one row
+// per step, with layer 6 on the vector units, 1824 us; two rows per step 1571;
+// this 1396 (890 TFLOP/s of the 32 -> 32 layers alone).
 constexpr int FW = 64, FV = FW - 10, FY = 256, FRC = FW + 2;  // frame, strip, rows per workgroup, ring columns
 constexpr int FTHREADS = 512;
 constexpr int RSL = 6;        // ring slots: four rows read, two written in the same step
@@ -595,16 +594,21 @@ constexpr int URS = 32;       // ubar ring rows
 constexpr int UBATCH = 6;     // ubar rows loaded together, every three steps
 static_assert(UBATCH * FRC <= FTHREADS, "one ubar value per thread");
 constexpr size_t kRingBytes = (size_t)(NL - 1) * RSL * RROW * sizeof(bf16);
-constexpr size_t kURingBytes = (size_t)URS * URC * sizeof(u32x2);
+constexpr size_t kURingBytes = (size_t)URS * URC * sizeof(float);
 constexpr size_t kFusedLds = kRingBytes + kURingBytes + (size_t)RSL * 3 * FW * sizeof(f32x4);
 static_assert(kFusedLds <= 160 * 1024, "LDS of one CU");
+
+// a value that is the same in every lane, in a scalar register
+__device__ __forceinline__ float uniform(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
 
 template <typename T>
 __global__ __launch_bounds__(FTHREADS) void k_fwd2d_fused(const T *ub, const double *s, const bf16 *wbf,
                                                           const float *params, Offsets off, float *z, int H, int W) {
     extern __shared__ __attribute__((aligned(16))) unsigned char fused_lds[];
     bf16 *ring = reinterpret_cast<bf16 *>(fused_lds);                  // [layer 2..6][slot RSL][FRC][C]
-    u32x2 *uring = reinterpret_cast<u32x2 *>(fused_lds + kRingBytes);  // ubar / s: [row slot URS][URC]
+    float *uring = reinterpret_cast<float *>(fused_lds + kRingBytes);  // ubar / s: [row slot URS][URC]
     // layer 6's products: [slot RSL][taps 4 t .. 4 t + 3][frame column]
     f32x4 *zring = reinterpret_cast<f32x4 *>(fused_lds + kRingBytes + kURingBytes);
     // channels 8 c .. 8 c + 7 of a ring column, in slot 0 of layer l's input;
@@ -634,24 +638,19 @@ __global__ __launch_bounds__(FTHREADS) void k_fwd2d_fused(const T *ub, const dou
     f32x16 mb;  // biases of the output channels this lane holds: the accumulator's start
 #pragma unroll
     for (int v = 0; v < 16; ++v) mb[v] = params[off.b[ML - 1] + 8 * (v >> 2) + 4 * kh + (v & 3)];
-    // layers 1 and 6: wave w takes frame columns 16 (w % 4) .. of the step's
-    // first (w < 4) or second row, lane group g = lane / 16 a quarter of the
-    // reduction.  Layer 1's has the slots 4 t .. 4 t + 2 for the three terms of
-    // tap t < 8, and slots 3, 7 and 11 for those of tap 8.
-    const int orow = wave >> 2, pcol = 16 * (wave & 3) + (lane & 15), g4 = lane >> 4;
-    bf16x8 W1f[2], W6f;
-    f32x4 b1[2];
+    // layer 1: wave w takes channels 4 w .. 4 w + 3, so its weights are uniform
+    // across the wave
+    float w1r[4][9], b1r[4];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int ch = 16 * h + (lane & 15);
+    for (int k = 0; k < 4; ++k) {
+        b1r[k] = uniform(params[off.b[0] + 4 * wave + k]);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int k = 8 * g4 + e, t = (k & 3) < 3 ? k >> 2 : (k < 12 ? 8 : -1);
-            W1f[h][e] = t >= 0 ? wbf[off.W[0] + ch * 9 + t] : (bf16)0.0f;
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) b1[h][v] = params[off.b[0] + 16 * h + 4 * g4 + v];
+        for (int t = 0; t < 9; ++t) w1r[k][t] = uniform((float)wbf[off.W[0] + (4 * wave + k) * 9 + t]);
     }
+    // layer 6: wave w takes frame columns 16 (w % 4) .. of the step's first (w < 4)
+    // or second row, lane group g4 = lane / 16 a quarter of the channels
+    const int orow = wave >> 2, pcol = 16 * (wave & 3) + (lane & 15), g4 = lane >> 4;
+    bf16x8 W6f;
 #pragma unroll
     for (int e = 0; e < 8; ++e)
         W6f[e] = (lane & 15) < 9 ? wbf[off.W[NL - 1] + (lane & 15) * C + 8 * g4 + e] : (bf16)0.0f;
@@ -667,13 +666,8 @@ __global__ __launch_bounds__(FTHREADS) void k_fwd2d_fused(const T *ub, const dou
         const int rho = rho0 + ur;
         return ur < UBATCH && rho < nu ? (float)ubs[(int64_t)((((ys - 1 + rho) % H) + H) % H) * W + ux] * inv : 0.0f;
     };
-    // as the sum of three bf16 terms of 8 bits each, exact for the 24 bits of v
     auto u_store = [&](int rho0, float v) {
-        if (ur < UBATCH) {
-            const bf16 hi = (bf16)v, mid = (bf16)(v - (float)hi), lo = (bf16)(v - (float)hi - (float)mid);
-            const bf16x2 a = {hi, mid}, b = {lo, (bf16)0.0f};
-            uring[((rho0 + ur) & (URS - 1)) * URC + uc] = {__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b)};
-        }
+        if (ur < UBATCH) uring[((rho0 + ur) & (URS - 1)) * URC + uc] = v;
     };
     u_store(0, u_load(0));
     u_store(UBATCH, u_load(UBATCH));
@@ -690,12 +684,7 @@ __global__ __launch_bounds__(FTHREADS) void k_fwd2d_fused(const T *ub, const dou
     bf16 *wm[2];  // layer ML's outputs, 16 channels per lane
 #pragma unroll
     for (int g = 0; g < 2; ++g) wm[g] = at(ML + 1, 32 * mh + j + 1, 2 * kh + g);
-    bf16 *w1[2];  // layer 1's, 4 channels per lane and half
-#pragma unroll
-    for (int h = 0; h < 2; ++h) w1[h] = at(2, pcol + 1, 2 * h + (g4 >> 1)) + (g4 & 1) * 4;
-    // layer 1's operands: taps 2 g and 2 g + 1, and tap 8's terms for the free slots
-    const int t0 = 2 * g4, t1 = t0 + 1;
-    const uint32_t keep_x = g4 < 2 ? ~0u : 0u, keep_y = g4 == 0 ? 0xffff0000u : 0u;
+    bf16 *w1 = at(2, lane + 1, wave >> 1) + (wave & 1) * 4;  // layer 1's
     auto row = [&](int slot, bf16x8 (&A)[6]) {
 #pragma unroll
         for (int k = 0; k < 6; ++k) A[k] = *reinterpret_cast<const bf16x8 *>(am[k] + slot * RROW);
@@ -708,11 +697,13 @@ __global__ __launch_bounds__(FTHREADS) void k_fwd2d_fused(const T *ub, const dou
     auto step = [&](auto phase, int st) {
         constexpr int c = phase.value;
         constexpr int in_slot[4] = {2 * ((c + 1) % 3), 2 * ((c + 1) % 3) + 1, 2 * ((c + 2) % 3), 2 * ((c + 2) % 3) + 1};
-        auto uval = [&](int t) {  // ubar row ys + 2 st + orow + t / 3 - 1, frame column pcol + t % 3 - 1
-            return uring + ((2 * st + orow + t / 3) & (URS - 1)) * URC + pcol + t % 3;
-        };
-        const u32x2 ua = *uval(t0), ub1 = *uval(t1);
-        const uint32_t u8 = reinterpret_cast<const uint32_t *>(uval(8))[g4 == 0 ? 0 : 1];
+        float xv[4][3];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {  // frame column lane + dx - 1
+            const float *u = uring + ((2 * st + r) & (URS - 1)) * URC + lane;
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) xv[r][dx] = u[dx];
+        }
         const bf16x8 A6 = *reinterpret_cast<const bf16x8 *>(a6 + (orow ? in_slot[3] : in_slot[2]) * RROW);
         __builtin_amdgcn_sched_barrier(0);
         f32x16 acc[2] = {mb, mb};
@@ -727,16 +718,16 @@ __global__ __launch_bounds__(FTHREADS) void k_fwd2d_fused(const T *ub, const dou
                         acc[o] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Wf[dy * 6 + k], A[g & 1][k], acc[o], 0, 0, 0);
                 }
         };
-        auto layer1 = [&]() {
-            const u32x4 x = {ua[0], ua[1] | (u8 & keep_x) << 16, ub1[0], ub1[1] | (u8 & keep_y)};
+        auto layer1 = [&](int o) {
+            alignas(8) bf16 v1[4];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const f32x4 d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W1f[h], __builtin_bit_cast(bf16x8, x), b1[h], 0, 0, 0);
-                alignas(8) bf16 v[4];
+            for (int k = 0; k < 4; ++k) {
+                float v = b1r[k];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) v[k] = (bf16)relu_bits(d[k]);
-                *reinterpret_cast<uint2 *>(w1[h] + (orow ? 2 * c + 1 : 2 * c) * RROW) = *reinterpret_cast<const uint2 *>(v);
+                for (int t = 0; t < 9; ++t) v += w1r[k][t] * xv[o + t / 3][t % 3];
+                v1[k] = (bf16)relu_bits(v);
             }
+            *reinterpret_cast<uint2 *>(w1 + (2 * c + o) * RROW) = *reinterpret_cast<const uint2 *>(v1);
         };
         auto write = [&](int o) {
             const Packed v = conv_pack<kFused>(acc[o], mb);
@@ -745,10 +736,11 @@ __global__ __launch_bounds__(FTHREADS) void k_fwd2d_fused(const T *ub, const dou
                 *reinterpret_cast<uint4 *>(wm[g] + (2 * c + o) * RROW) = *reinterpret_cast<const uint4 *>(v.q + 4 * g);
         };
         products(0);
-        layer1();
+        layer1(0);
         __builtin_amdgcn_sched_barrier(0);
         row(in_slot[2], A[0]);
         products(1);
+        layer1(1);
         const f32x4 d6 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W6f, A6, f32x4{}, 0, 0, 0);
         if (g4 < 3) z6[(orow ? 2 * c + 1 : 2 * c) * 3 * FW] = d6;
         __builtin_amdgcn_sched_barrier(0);
