@@ -192,9 +192,14 @@ __device__ __forceinline__ void load_items(int count, L &&load, S &&store) {
 // transform.  BOTH: forward, multiplier and inverse in one pass, the values in
 // LDS between (3 x 256^3 FP64: 310 us, as two passes
 // 416).
-template <typename T, bool INV, bool BOTH = false>
+// BAND: the values transformed back are the band projection's, (X0 - XB) / N
+// on the modes where |XB|^2 is above the field's threshold and 0 elsewhere,
+// formed from both spectra as they are loaded.
+enum ColMode { COL_PLAIN, COL_BOTH, COL_BAND };
+template <typename T, bool INV, ColMode MODE = COL_PLAIN>
 __global__ __launch_bounds__(256) void k_fft_cols(T *data, int64_t inner, int n, int logn, int logcw, int64_t nchunks,
-                                                  SpecMap m) {
+                                                  SpecMap m, const T *xb, const double *thr, int thr_stride) {
+    constexpr bool BOTH = MODE == COL_BOTH, BAND = MODE == COL_BAND;
     using V = typename V2<T>::t;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     V *buf = reinterpret_cast<V *>(lds_raw);
@@ -215,11 +220,21 @@ __global__ __launch_bounds__(256) void k_fft_cols(T *data, int64_t inner, int n,
         if (m.axis == 1) return mul_at(m, ii, j, m.ndim == 3 ? o % m.nz : 0);
         return mul_at(m, ii % m.nxh, ii / m.nxh, j);
     };
+    const V *band = BAND ? reinterpret_cast<const V *>(xb) + (o * n) * inner + i0 : nullptr;
+    const double level = BAND ? thr[o * thr_stride] : 0.0, inv_n = 1.0 / m.npts;
     load_items(
         n << logcw,
         [&](int idx) {
             const int c = idx & (cw - 1), j = idx >> logcw;
-            return c < ncols ? base[(int64_t)j * inner + c] : V{T(0), T(0)};
+            const V zero = {T(0), T(0)};
+            const V z = c < ncols ? base[(int64_t)j * inner + c] : zero;
+            if constexpr (BAND) {
+                const V zb = c < ncols ? band[(int64_t)j * inner + c] : zero;
+                const double p = (double)zb.x * (double)zb.x + (double)zb.y * (double)zb.y;
+                if (!(c < ncols && (i0 + c) % m.nxh < m.nxc && p > level)) return zero;
+                return V{(T)(((double)z.x - (double)zb.x) * inv_n), (T)(((double)z.y - (double)zb.y) * inv_n)};
+            }
+            return z;
         },
         [&](int idx, V v) {
             const int c = idx & (cw - 1), j = idx >> logcw;
@@ -294,10 +309,10 @@ __global__ __launch_bounds__(256) void k_rfft_rows(const T *x, T *X, int64_t nro
 }
 
 // Inverse real rows: X (rows of nxh complex, k = 0 .. nx/2 used) -> x, the
-// unnormalised inverse (nx times the inverse DFT along x).
-template <typename T>
-__global__ __launch_bounds__(256) void k_irfft_rows(const T *X, T *x, int64_t nrows, int nx, int logn2, int64_t nxh,
-                                                    int logrpw) {
+// unnormalised inverse (nx times the inverse DFT along x); ADD: x = that + y.
+template <typename T, bool ADD>
+__global__ __launch_bounds__(256) void k_irfft_rows(const T *X, T *x, const T *y, int64_t nrows, int nx, int logn2,
+                                                    int64_t nxh, int logrpw) {
     using V = typename V2<T>::t;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     V *buf = reinterpret_cast<V *>(lds_raw);
@@ -328,7 +343,12 @@ __global__ __launch_bounds__(256) void k_irfft_rows(const T *X, T *x, int64_t nr
     V *dst = reinterpret_cast<V *>(x + r0 * nx);
     for (int idx = threadIdx.x; idx < n2 * nr; idx += 256) {
         const int r = idx >> logn2, j = idx & (n2 - 1);
-        dst[(int64_t)r * n2 + j] = buf[(j << logrpw) + r];
+        V v = buf[(j << logrpw) + r];
+        if constexpr (ADD) {
+            const V w = reinterpret_cast<const V *>(y + r0 * nx)[(int64_t)r * n2 + j];
+            v = {v.x + w.x, v.y + w.y};
+        }
+        dst[(int64_t)r * n2 + j] = v;
     }
 }
 
@@ -402,9 +422,11 @@ SpecMap map_of(const Spec &s, int axis, int mul, double inv_kc2) {
     return m;
 }
 
-enum Dir { FORWARD, INVERSE, THERE_AND_BACK };
+// INVERSE_BAND: of the band projection of data against the spectra xb, thr[b * thr_stride] the threshold of field b
+enum Dir { FORWARD, INVERSE, THERE_AND_BACK, INVERSE_BAND };
 template <typename T>
-int launch_cols(const Spec &s, T *data, int axis, Dir dir, int mul, double inv_kc2, hipStream_t st) {
+int launch_cols(const Spec &s, T *data, int axis, Dir dir, int mul, double inv_kc2, hipStream_t st,
+                const T *xb = nullptr, const double *thr = nullptr, int thr_stride = 0) {
     const int64_t n = axis == 1 ? s.ny : s.nz;
     const int64_t inner = axis == 1 ? s.nxh : s.ny * s.nxh;
     const int64_t outer = axis == 1 ? s.batch * s.nz : s.batch;
@@ -417,10 +439,12 @@ int launch_cols(const Spec &s, T *data, int axis, Dir dir, int mul, double inv_k
     if (blocks > 0x7fffffff) return fail(GD_EINVAL, "grid too large for the FFT");
     const SpecMap m = map_of(s, axis, mul, inv_kc2);
     const size_t lds = (size_t)n * cw * cs;
-    const auto kern = dir == FORWARD   ? k_fft_cols<T, false>
-                      : dir == INVERSE ? k_fft_cols<T, true>
-                                       : k_fft_cols<T, false, true>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), lds, st, data, inner, (int)n, ilog2(n), logcw, nchunks, m);
+    const auto kern = dir == FORWARD          ? k_fft_cols<T, false>
+                      : dir == INVERSE        ? k_fft_cols<T, true>
+                      : dir == THERE_AND_BACK ? k_fft_cols<T, false, COL_BOTH>
+                                              : k_fft_cols<T, true, COL_BAND>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), lds, st, data, inner, (int)n, ilog2(n), logcw, nchunks, m,
+                       xb, thr, thr_stride);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? GD_OK : fail(GD_EHIP, "FFT column launch: %s", hipGetErrorString(e));
 }
@@ -448,14 +472,16 @@ int launch_rfft_rows(const Spec &s, const T *x, T *X, hipStream_t st) {
     return e == hipSuccess ? GD_OK : fail(GD_EHIP, "FFT row launch: %s", hipGetErrorString(e));
 }
 
+// x = the inverse of X's rows, plus `add` where it is given
 template <typename T>
-int launch_irfft_rows(const Spec &s, const T *X, T *x, hipStream_t st) {
+int launch_irfft_rows(const Spec &s, const T *X, T *x, hipStream_t st, const T *add = nullptr) {
     const int64_t nrows = s.batch * s.nz * s.ny;
     const int lr = log_rows_per_wg<T>(s), rpw = 1 << lr;
     const int64_t blocks = (nrows + rpw - 1) / rpw;
     const size_t lds = (size_t)(s.nx / 2) * rpw * 2 * sizeof(T);
-    hipLaunchKernelGGL((k_irfft_rows<T>), dim3((unsigned)blocks), dim3(256), lds, st, X, x, nrows, (int)s.nx,
-                       ilog2(s.nx / 2), s.nxh, lr);
+    const auto kern = add ? k_irfft_rows<T, true> : k_irfft_rows<T, false>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), lds, st, X, x, add, nrows, (int)s.nx, ilog2(s.nx / 2),
+                       s.nxh, lr);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? GD_OK : fail(GD_EHIP, "FFT row launch: %s", hipGetErrorString(e));
 }
@@ -719,38 +745,21 @@ __global__ __launch_bounds__(256) void k_band_power(const T *X, double *part, in
     if (threadIdx.x == 0) part[b * nchunks + ch] = red[0];
 }
 
-// X0 <- (X0 - XB) / N on the modes where |XB|^2 > tau E_b, 0 elsewhere, with
-// E_b = (1/N) sum_k w |XB|^2 the mean of |XB(k)|^2 over all N wavenumbers of
-// field b (= sum_x ubar^2, Parseval).  The 1/N makes the unnormalized
-// inverse transform the inverse.
-template <typename T>
-__global__ __launch_bounds__(256) void k_band_mask(T *X0, const T *XB, const double *part, int64_t per_field,
-                                                   int64_t nchunks, Spec s, double tau) {
-    using V = typename V2<T>::t;
-    __shared__ double thr;
-    const int64_t b = blockIdx.y;
-    const double n = (double)(s.nx * s.ny * s.nz);
-    if (threadIdx.x == 0) {
-        double e = 0.0;
-        for (int64_t c = 0; c < nchunks; ++c) e += part[b * nchunks + c];
-        thr = tau * (e / n);
-    }
+// The projection is (X0 - XB) / N on the modes where |XB|^2 > tau E_b, 0
+// elsewhere, with E_b = (1/N) sum_k w |XB|^2 the mean of |XB(k)|^2 over all N
+// wavenumbers of field b (= sum_x ubar^2, Parseval); the 1/N makes the
+// unnormalized inverse transform the inverse.  The first inverse column pass
+// forms it (k_fft_cols, BAND), and the inverse rows add ubar: as passes of
+// their own these took 68 and 31 of 330 us for 16 x 1024^2.  Here tau E_b, the
+// chunks' sums added in order, takes the place of field b's first chunk.
+__global__ __launch_bounds__(256) void k_band_level(double *part, int nchunks, double n, double tau) {
+    __shared__ double p[256];
+    if ((int)threadIdx.x < nchunks) p[threadIdx.x] = part[(int64_t)blockIdx.x * nchunks + threadIdx.x];
     __syncthreads();
-    const double t = thr, inv_n = 1.0 / n;
-    V *F0 = reinterpret_cast<V *>(X0) + b * per_field;
-    const V *FB = reinterpret_cast<const V *>(XB) + b * per_field;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < per_field; i += (int64_t)gridDim.x * 256) {
-        const int64_t kx = i % s.nxh;
-        const V zb = FB[i], z0 = F0[i];
-        const double p = (double)zb.x * (double)zb.x + (double)zb.y * (double)zb.y;
-        V r;
-        r.x = r.y = T(0);
-        if (kx < s.nxc && p > t) {
-            r.x = (T)(((double)z0.x - (double)zb.x) * inv_n);
-            r.y = (T)(((double)z0.y - (double)zb.y) * inv_n);
-        }
-        F0[i] = r;
-    }
+    if (threadIdx.x != 0) return;
+    double e = 0.0;
+    for (int c = 0; c < nchunks; ++c) e += p[c];
+    part[(int64_t)blockIdx.x * nchunks] = tau * (e / n);
 }
 
 // The same projection on the Parseval-scaled spectra the differential-filter
@@ -783,12 +792,6 @@ __global__ __launch_bounds__(256) void k_band_keep(T *U, const T *UB, const doub
     }
 }
 
-// u0 += ubar
-template <typename T>
-__global__ __launch_bounds__(256) void k_band_add(T *u0, const T *ubar, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) u0[i] += ubar[i];
-}
-
 // threshold of the band projection a warm start of the differential-filter
 // solve gets (relative to the mean mode power of ubar)
 constexpr double kWarmBandTau = 1e-10;
@@ -811,16 +814,14 @@ int band_project_run(const Spec &s, double tau, const T *ubar, T *u0, char *w, h
     if (s.batch > 65535) return fail(GD_EINVAL, "batch too large for the band projection (at most 65535 fields)");
     hipLaunchKernelGGL(k_band_power<T>, dim3((unsigned)nch, (unsigned)s.batch), dim3(256), 0, st, XB, part, per_field,
                        nch, s);
-    const unsigned mb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((per_field + 255) / 256, 1024));
-    hipLaunchKernelGGL(k_band_mask<T>, dim3(mb, (unsigned)s.batch), dim3(256), 0, st, X0, XB, part, per_field, nch, s,
-                       tau);
-    hipError_t e = hipGetLastError();
+    hipLaunchKernelGGL(k_band_level, dim3((unsigned)s.batch), dim3(256), 0, st, part, (int)nch,
+                       (double)(s.nx * s.ny * s.nz), tau);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(GD_EHIP, "band projection launch: %s", hipGetErrorString(e));
-    if ((rc = inverse<T>(s, X0, u0, MUL_NONE, 0.0, st))) return rc;
-    const int64_t npts = s.batch * s.nx * s.ny * s.nz;
-    hipLaunchKernelGGL(k_band_add<T>, dim3(stride_blocks(npts)), dim3(256), 0, st, u0, ubar, npts);
-    e = hipGetLastError();
-    return e == hipSuccess ? GD_OK : fail(GD_EHIP, "band projection launch: %s", hipGetErrorString(e));
+    if ((rc = launch_cols<T>(s, X0, s.ndim == 3 ? 2 : 1, INVERSE_BAND, MUL_NONE, 0.0, st, XB, part, (int)nch)))
+        return rc;
+    if (s.ndim == 3 && (rc = launch_cols<T>(s, X0, 1, INVERSE, MUL_NONE, 0.0, st))) return rc;
+    return launch_irfft_rows<T>(s, X0, u0, st, ubar);
 }
 
 __global__ void k_zero_i64(int64_t *p, int64_t n) {
