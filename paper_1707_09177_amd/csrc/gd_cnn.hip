@@ -172,7 +172,7 @@ __global__ void k_rms_fin(const double *part, int B, int64_t P, double *s) {
 // from bf16 at every use and 16-byte stores 64 bytes apart, took 578 us for
 // 4 x 128^3 (64 us for 8 x 512^2; the input gradient 77 us); this takes
 // 267 us (38 and 62 us).
-constexpr int EPT = 4, EZ = 16;  // rows per thread; planes per run
+constexpr int EPT = 4, EZ = 16;  // rows per thread; most planes per run
 // LDS position (in 16-byte chunks) of chunk c of point pix: the four chunks of
 // a point are permuted by its index, so that the 16-byte accesses of 8
 // adjacent points hit 8 different bank groups
@@ -180,7 +180,7 @@ __device__ __forceinline__ int swz(int pix, int c) { return pix * 4 + (c ^ ((pix
 template <typename T, int NT, bool GRAD>
 __global__ __launch_bounds__(256) void k_conv_end(const T *in, const double *s, const float *__restrict__ wt,
                                                   const float *__restrict__ bias, const bf16 *mask, bf16 *out, int H,
-                                                  int W, int nz, int tiles_x, int tiles_y, int zruns) {
+                                                  int W, int nz, int tiles_x, int tiles_y, int zruns, int zrun) {
     constexpr int ND = NT / 9;
     __shared__ uint4 stage[4][EPT][64 * 4];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256) void k_conv_end(const T *in, const double *s, 
     const int64_t smp = rest / zruns;
     if (y0 >= H) return;  // the whole wave
     const int64_t HW = (int64_t)H * W;
-    const int zlo = zr * EZ, zhi = min(nz, zlo + EZ);
+    const int zlo = zr * zrun, zhi = min(nz, zlo + zrun);
     const float inv = GRAD ? 1.0f : (float)(1.0 / s[smp]);
     const int xm = wrap(x - 1, W), xp = wrap(x + 1, W);
     float v[ND][EPT + 2][3];
@@ -784,12 +784,12 @@ __global__ __launch_bounds__(FTHREADS) void k_fwd2d_fused(const T *ub, const dou
 // registers, so an activation is read once and not once per tap.
 // Bound by that read: reading 64 bytes per tap and point took 1191 us for
 // 4 x 128^3 (113 us for 8 x 512^2); this takes 137 (29) us.
-constexpr int OY = 16, OX = 32, OZ = 16;
+constexpr int OY = 16, OX = 32, OZ = 16;  // OZ: most planes per run
 constexpr int OPTS = (OY + 2) * (OX + 2), OGRP = (OPTS + 31) / 32;  // tile points with the halo, groups of 32
 constexpr int OST = OGRP * 32;                                      // LDS row of one tap
 template <int NT>
 __global__ __launch_bounds__(256) void k_conv_out(const bf16 *a, const bf16 *w6, const float *b6, float *z, int H,
-                                                  int W, int nz, int tiles_x, int tiles_y, int zruns) {
+                                                  int W, int nz, int tiles_x, int tiles_y, int zruns, int zrun) {
     constexpr int ND = NT / 9;
     constexpr int GPW = (OGRP + 3) / 4;  // groups per wave
     __shared__ float D[NT * OST];
@@ -799,7 +799,7 @@ __global__ __launch_bounds__(256) void k_conv_out(const bf16 *a, const bf16 *w6,
     const int zr = (int)(rest % zruns);
     const int64_t smp = rest / zruns, HW = (int64_t)H * W;
     // 2D: every plane is a sample of its own (nz = 1)
-    const int zlo = zr * OZ, zhi = min(nz, zlo + OZ);
+    const int zlo = zr * zrun, zhi = min(nz, zlo + zrun);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int j = lane & 31, kh = lane >> 5;
     // weights: row = tap (rows past NT are zero), k = channel
@@ -1446,29 +1446,40 @@ int mid_layer(bool bwd, const gd_grid *g, const bf16 *in, const bf16 *slices, co
                : launch_mid2<kFwd>(g, in, slices, bias, mask, out, st);
 }
 
+// Planes per run of a 3D end layer: at most `most`, fewer (at least `least`)
+// where that leaves fewer than `want` workgroups.  A run loads two planes more
+// than it has.  1 x 32^3 with runs of 16: layer 1 131 us, layer 6 33 us, for 4
+// workgroups; with short runs the whole forward takes 89 us (125 before the
+// layers marched along z), 2 x 64^3 187 (470).
+int run_planes(int64_t cols, int nz, int most, int least, int64_t want) {
+    return (int)std::max<int64_t>(least, std::min<int64_t>(most, cols * nz / want));
+}
+
 // layer 1, or with mask the input gradient of layer 6 (in = dL/dz)
 template <typename T, bool GRAD>
 int end_layer(const gd_grid *g, const T *in, const double *s, const float *wt, const float *bias, const bf16 *mask,
               bf16 *out, hipStream_t st) {
     const int H = (int)g->n[1], W = (int)g->n[0], nz = g->ndim == 3 ? (int)g->n[2] : 1;
-    const int tiles_x = (W + 63) / 64, tiles_y = (H + 4 * EPT - 1) / (4 * EPT), zruns = (nz + EZ - 1) / EZ;
+    const int tiles_x = (W + 63) / 64, tiles_y = (H + 4 * EPT - 1) / (4 * EPT);
+    const int zrun = run_planes(g->batch * tiles_x * tiles_y, nz, EZ, 1, 1024), zruns = (nz + zrun - 1) / zrun;
     const int64_t blk = (int64_t)g->batch * tiles_x * tiles_y * zruns;
     if (blk > 0x7fffffff) return fail(GD_EINVAL, "field too large");
     auto k2 = k_conv_end<T, 9, GRAD>;
     auto k3 = k_conv_end<T, 27, GRAD>;
     GD_LAUNCH(g->ndim == 2 ? k2 : k3, dim3((unsigned)blk), dim3(256), 0, st, in, s, wt, bias, mask, out, H, W, nz,
-              tiles_x, tiles_y, zruns);
+              tiles_x, tiles_y, zruns, zrun);
     return GD_OK;
 }
 
 // layer 6
 int out_layer(const gd_grid *g, const bf16 *a, const bf16 *w6, const float *b6, float *z, hipStream_t st) {
     const int H = (int)g->n[1], W = (int)g->n[0], nz = g->ndim == 3 ? (int)g->n[2] : 1;
-    const int tiles_x = (W + OX - 1) / OX, tiles_y = (H + OY - 1) / OY, zruns = (nz + OZ - 1) / OZ;
+    const int tiles_x = (W + OX - 1) / OX, tiles_y = (H + OY - 1) / OY;
+    const int zrun = run_planes(g->batch * tiles_x * tiles_y, nz, OZ, 2, 512), zruns = (nz + zrun - 1) / zrun;
     const int64_t blk = (int64_t)g->batch * tiles_x * tiles_y * zruns;
     if (blk > 0x7fffffff) return fail(GD_EINVAL, "field too large");
     GD_LAUNCH(g->ndim == 2 ? k_conv_out<9> : k_conv_out<27>, dim3((unsigned)blk), dim3(256), 0, st, a, w6, b6, z, H, W,
-              nz, tiles_x, tiles_y, zruns);
+              nz, tiles_x, tiles_y, zruns, zrun);
     return GD_OK;
 }
 
