@@ -174,9 +174,9 @@ __device__ __forceinline__ double mul_at(const SpecMap &m, int64_t kx, int64_t k
 // 223 (eight: 212, 221; the inverse rows' pairs gain nothing).
 constexpr int kLoads = 4;
 template <typename L, typename S>
-__device__ __forceinline__ void load_items(int count, L &&load, S &&store) {
+__device__ __forceinline__ void load_items(int count, bool many, L &&load, S &&store) {
     int i0 = threadIdx.x;
-    for (; i0 + (kLoads - 1) * 256 < count; i0 += kLoads * 256) {
+    for (; many && i0 + (kLoads - 1) * 256 < count; i0 += kLoads * 256) {
         decltype(load(0)) v[kLoads];
 #pragma unroll
         for (int k = 0; k < kLoads; ++k) v[k] = load(i0 + k * 256);
@@ -220,10 +220,19 @@ __global__ __launch_bounds__(256) void k_fft_cols(T *data, int64_t inner, int n,
         if (m.axis == 1) return mul_at(m, ii, j, m.ndim == 3 ? o % m.nz : 0);
         return mul_at(m, ii % m.nxh, ii / m.nxh, j);
     };
+    // The Parseval scales depend on the column alone, and a thread's items are
+    // of one column.  Where a workgroup takes pieces of less than 32 bytes from a
+    // row, its neighbours need the rest of the cache line, and the faster a
+    // workgroup loads, the less of it they find in L2: there a value is loaded and
+    // scaled at a time (16 x 2048^2 FP32 inverse 316 us, with wide loads 386; 32 x
+    // 1024^2, in pieces of 32 bytes, 129 -> 114).
+    const int col = threadIdx.x & (cw - 1);
+    const bool scaled = !BOTH && m.mul != MUL_NONE, wide = cw * sizeof(V) >= 32;
+    const T scale = scaled && wide && col < ncols ? T(mult(0, col)) : T(1);
     const V *band = BAND ? reinterpret_cast<const V *>(xb) + (o * n) * inner + i0 : nullptr;
     const double level = BAND ? thr[o * thr_stride] : 0.0, inv_n = 1.0 / m.npts;
     load_items(
-        n << logcw,
+        n << logcw, wide,
         [&](int idx) {
             const int c = idx & (cw - 1), j = idx >> logcw;
             const V zero = {T(0), T(0)};
@@ -238,9 +247,9 @@ __global__ __launch_bounds__(256) void k_fft_cols(T *data, int64_t inner, int n,
         },
         [&](int idx, V v) {
             const int c = idx & (cw - 1), j = idx >> logcw;
-            if (INV && m.mul != MUL_NONE && c < ncols) {
-                const T s = T(mult(j, c));
-                v = {v.x * s, v.y * s};
+            if (INV && scaled && c < ncols) {
+                const T f = wide ? scale : T(mult(j, c));
+                v = {v.x * f, v.y * f};
             }
             buf[(bitrev(j, logn) << logcw) + c] = v;
         });
@@ -264,9 +273,9 @@ __global__ __launch_bounds__(256) void k_fft_cols(T *data, int64_t inner, int n,
         const int c = idx & (cw - 1), j = idx >> logcw;
         if (c >= ncols) continue;
         V v = buf[(j << logcw) + c];
-        if (!INV && !BOTH && m.mul != MUL_NONE) {
-            const T s = T(mult(j, c));
-            v = {v.x * s, v.y * s};
+        if (!INV && scaled) {
+            const T f = wide ? scale : T(mult(j, c));
+            v = {v.x * f, v.y * f};
         }
         base[(int64_t)j * inner + c] = v;
     }
@@ -285,7 +294,7 @@ __global__ __launch_bounds__(256) void k_rfft_rows(const T *x, T *X, int64_t nro
     const int nr = (int)std::min<int64_t>(rpw, nrows - r0);
     const V *src = reinterpret_cast<const V *>(x + r0 * nx);  // z[j] = x[2j] + i x[2j+1]
     load_items(
-        n2 << logrpw, [&](int idx) { return idx >> logn2 < nr ? src[idx] : V{T(0), T(0)}; },
+        n2 << logrpw, true, [&](int idx) { return idx >> logn2 < nr ? src[idx] : V{T(0), T(0)}; },
         [&](int idx, V v) { buf[(bitrev(idx & (n2 - 1), logn2) << logrpw) + (idx >> logn2)] = v; });
     __syncthreads();
     lds_fft<T, false>(buf, n2, logn2, logrpw);
