@@ -22,7 +22,7 @@ __global__ void k_res_prep(uint64_t *slot, int64_t nslot, uint32_t *flag, int64_
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, n = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = t; i < nslot; i += n) slot[i] = 0;
     for (int64_t i = t; i < nflag; i += n) flag[i] = 0;
-    if (t == 0) *abort = 0;
+    if (t == 0) abort[0] = abort[kEnded] = 0;
 }
 
 const void *kernel_of(int dtype, int ndim, int solver, const Plan &p) {

@@ -57,13 +57,15 @@ constexpr int most_points(int solver, int ndim, int tsize) {
     return solver != GD_BICGSTAB && (solver == GD_CG || ndim == 3) ? points(tsize) * 3 / 2 : points(tsize);
 }
 
+constexpr int kEnded = 32;   // word of the abort line that counts ended workgroups
+
 struct Params {
     const void *ubar;
     void *u;
     void *xch;          // exchange buffer: boundary points at their place in the field
     uint64_t *slot;     // [cluster][2][W][kWords]
     uint32_t *flag;     // [cluster][W][32]: exchanges published
-    uint32_t *abort;
+    uint32_t *abort;    // [0] set when a wait exceeded its bound, [kEnded] workgroups that have ended
     gd_info *info;
     double *hist;
     int64_t npts, batch, nclusters, hist_stride, wait_ticks;
@@ -589,14 +591,30 @@ __global__ __launch_bounds__(kThreads) void k_resident(Params P) {
             out.r_true = r_true;
             out.start = start;
             out.replaced = nrep;
-            P.info[fld] = out;
+            // no part of the record stays in this L2: another workgroup may write its status
+            static_assert(sizeof(gd_info) == 6 * sizeof(uint64_t));
+            uint64_t rec[6];
+            __builtin_memcpy(rec, &out, sizeof out);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) st_agent(reinterpret_cast<uint64_t *>(P.info + fld) + k, rec[k]);
         }
     }
     if (!ok && wg == 0 && tid == 0)
         for (; fld < P.batch; fld += P.nclusters) {
-            P.info[fld].status = GD_TIMEOUT;
-            P.info[fld].iters = 0;
+            st_agent(&P.info[fld].status, (int32_t)GD_TIMEOUT);
+            st_agent(&P.info[fld].iters, 0);
         }
+    // A workgroup gives up by itself, so after a reduction some may have gone
+    // on and others not: workgroup 0 may have written the record of a field
+    // whose other boxes were not stored.  The workgroup that ends last sees
+    // whether any gave up, and marks every field then.
+    if (P.W > 1 && tid == 0) {
+        gd::wait_vm_stores();
+        const uint32_t n =
+            __hip_atomic_fetch_add(P.abort + kEnded, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (n == gridDim.x - 1 && ld_agent(P.abort))
+            for (int64_t b = 0; b < P.batch; ++b) st_agent(&P.info[b].status, (int32_t)GD_TIMEOUT);
+    }
 }
 
 }  // namespace gdres

@@ -1,0 +1,38 @@
+"""A bound on the waits of a solve that one of them exceeds: GD_TIMEOUT in every
+info record, also where some workgroups or fields had finished before.  Forced
+from the host by a bound of a few microseconds: every workgroup ends normally.
+"""
+import pytest
+import torch
+
+from paper_1707_09177_amd import gdecon
+
+pytestmark = pytest.mark.gpu
+
+RESIDENT = 10000
+
+
+# fields of several boxes in several rounds: some end before a wait is too long
+@pytest.mark.parametrize("shape, nd, N", [((200, 200, 300), 2, 6), ((30, 1000, 1000), 2, 3), ((64, 64, 64, 64), 3, 2)],
+                         ids=["200x200x300", "30x1000x1000", "64x64x64x64"])
+def test_resident_timeout_is_in_every_record(shape, nd, N):
+    """A solve either times out as a whole or is the one without a bound, bit for bit."""
+    ub = gdecon.filter_apply(torch.randn(shape, device="cuda", generator=torch.Generator("cuda").manual_seed(1)), ndim=nd)
+    d = gdecon.Deconvolver(ub.shape, nd, ub.dtype, "bicgstab")
+    want = torch.empty_like(ub)
+    full = d.solve(ub, N, out=want).info()
+    assert gdecon.last_launch()["variant"] >= RESIDENT and gdecon.last_launch()["tiles"] > shape[0]
+    out = torch.empty_like(ub)
+    timed_out = 0
+    for limit in (1, 2, 2, 2, 2, 3, 3, 3, 3, 4, 4, 4, 5, 5, 6):
+        out.fill_(float("nan"))
+        info = d.solve(ub, N, out=out, wait_limit_us=limit).info()
+        names = {i["status_name"] for i in info}
+        assert len(names) == 1, (limit, [i["status_name"] for i in info])
+        if names == {"TIMEOUT"}:
+            timed_out += 1
+        else:
+            assert info == full and torch.equal(out, want), limit
+    assert timed_out >= 1
+    out.fill_(float("nan"))
+    assert d.solve(ub, N, out=out).info() == full and torch.equal(out, want)
