@@ -116,7 +116,10 @@ __global__ __launch_bounds__(256) void k_fold(const T *X, Params P) {
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, nt = (int64_t)gridDim.x * 256;
     if (blockIdx.y == 0) {
         for (int64_t i = t; i < P.nslots; i += nt) P.slot[i] = 0;
-        for (int64_t i = t; i < P.batch; i += nt) P.done[i] = 0;
+        for (int64_t i = t; i < P.batch; i += nt) {
+            P.done[i] = 0;
+            P.rec[i] = Rec{};  // what a solve that is ended by the wait bound leaves of its fields
+        }
         if (t == 0) P.ctl->abort = 0;
     }
     const int lane = threadIdx.x & 63;

@@ -36,3 +36,24 @@ def test_resident_timeout_is_in_every_record(shape, nd, N):
     assert timed_out >= 1
     out.fill_(float("nan"))
     assert d.solve(ub, N, out=out).info() == full and torch.equal(out, want)
+
+
+def test_class_solve_timeout_leaves_no_workspace_bytes():
+    """The differential filter's solve on classes: the records of a timed-out solve
+    hold what its fields had, not what the workspace held before."""
+    ub = gdecon.germano_filter(torch.randn(40, 512, 512, device="cuda", dtype=torch.float64), 0.3)
+    d = gdecon.GermanoDeconvolver(ub.shape, 2, ub.dtype, "bicgstab", 0.3)
+    full = d.solve(ub, 6).info()
+    timed_out = 0
+    for limit in (1, 1, 2, 2, 3, 4):
+        d.work.fill_(255)
+        info = d.solve(ub, 6, wait_limit_us=limit).info()
+        names = {i["status_name"] for i in info}
+        assert len(names) == 1
+        if names == {"TIMEOUT"}:
+            timed_out += 1
+            for i, f in zip(info, full):
+                assert i["iters"] in (0, f["iters"]) and i["r_ref"] in (0.0, f["r_ref"]), i
+        else:
+            assert info == full
+    assert timed_out >= 1
