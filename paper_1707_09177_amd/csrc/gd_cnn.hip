@@ -317,22 +317,27 @@ __device__ __forceinline__ int64_t xcd_order() {
 __device__ __forceinline__ int tile_at(int row, int col, int c) { return (row * TXH + col) * 4 + (c ^ ((col >> 1) & 3)); }
 
 // A plane's tile (rows y0 - 1 .., columns x0 - 1 .., periodic) is loaded in
-// 16-byte pieces, piece k 256 + thread by a thread: its place in the plane, in pieces
+// 16-byte pieces, piece k 256 + thread by a thread: one of the four chunks of a
+// point.  A plane has up to 2^31 - 1 points, so a piece's place takes 33 bits:
+// the point and the chunk are apart until the load.
 constexpr int CH = (4 * RB + 2) * TXH * 4, CPL = (CH + 255) / 256;  // pieces, per thread
-__device__ __forceinline__ uint32_t tile_piece(int k, int x0, int y0, int H, int W) {
+struct Piece {
+    uint32_t point, chunk;
+};
+__device__ __forceinline__ Piece tile_piece(int k, int x0, int y0, int H, int W) {
     const int q = min(k * 256 + (int)threadIdx.x, CH - 1);
     const int pix = q >> 2, r = pix / TXH, cc = pix - r * TXH, c = (q & 3) ^ ((cc >> 1) & 3);
     int gy = y0 + r - 1, gx = x0 + cc - 1;
     gy = gy < 0 ? gy + H : (gy >= H ? (gy == H ? 0 : H - 1) : gy);  // points past the halo are not used
     gx = gx < 0 ? gx + W : (gx >= W ? (gx == W ? 0 : W - 1) : gx);
-    return ((uint32_t)gy * (uint32_t)W + (uint32_t)gx) * 4 + c;
+    return {(uint32_t)gy * (uint32_t)W + (uint32_t)gx, (uint32_t)c};
 }
-// start the load of piece k, `at` in the plane, into LDS
-__device__ __forceinline__ void stage_piece(const bf16 *plane, unsigned char *tile, int k, uint32_t at, int wave) {
+// start the load of piece k into LDS
+__device__ __forceinline__ void stage_piece(const bf16 *plane, unsigned char *tile, int k, Piece at, int wave) {
     if ((k + 1) * 256 <= CH || k * 256 + (int)threadIdx.x < CH)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(plane + (int64_t)at * 8),
-                                         (__attribute__((address_space(3))) void *)(tile + (k * 256 + wave * 64) * 16), 16,
-                                         0, 0);
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void *)(plane + (uint64_t)at.point * C + at.chunk * 8),
+            (__attribute__((address_space(3))) void *)(tile + (k * 256 + wave * 64) * 16), 16, 0, 0);
 }
 // wait for this wave's outstanding loads (vmcnt 0), tile loads included
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
@@ -494,13 +499,19 @@ __global__ __launch_bounds__(256, 1) void k_conv_mid3(const bf16 *in, const bf16
     const int j = lane & 31, kh = lane >> 5;
     constexpr size_t TB = kConvLds;
     // plane z (periodic) into ring slot (z - zlo + 1) mod 4
-    uint32_t piece[CPL];
+    uint32_t point[CPL], chunks = 0;  // the pieces' points, and two bits of chunk each
+    static_assert(CPL <= 16);
 #pragma unroll
-    for (int k = 0; k < CPL; ++k) piece[k] = tile_piece(k, x0, y0, H, W);
+    for (int k = 0; k < CPL; ++k) {
+        const Piece p = tile_piece(k, x0, y0, H, W);
+        point[k] = p.point;
+        chunks |= p.chunk << 2 * k;
+    }
     auto stage = [&](int z) {
         const bf16 *plane = in + (p0 + wrap(z, nz)) * HW * C;
 #pragma unroll
-        for (int k = 0; k < CPL; ++k) stage_piece(plane, conv_tile + (size_t)((z - zlo + 1) & 3) * TB, k, piece[k], wave);
+        for (int k = 0; k < CPL; ++k)
+            stage_piece(plane, conv_tile + (size_t)((z - zlo + 1) & 3) * TB, k, {point[k], chunks >> 2 * k & 3}, wave);
     };
     stage(zlo - 1);
     stage(zlo);
