@@ -1143,24 +1143,26 @@ __global__ __launch_bounds__(WGT, 3) void k_wgrad_mid(const bf16 *xa, const bf16
         return d;
     };
     const bf16x8 zero = {};
+    // this lane's column of a unit's gradient and, with the wave's shift, of its input
+    auto g_column = [&](const Unit &u) {
+        return ga + u.b * HW * C + (int64_t)min(u.x0 + j, W - 1) * C + kh * 8;
+    };
+    auto x_column = [&](const Unit &u) {
+        const int c = u.x0 + j + dx - 1;
+        return xa + plane_shift(u.b, nz, dzo) * HW * C + kh * 8 +
+               (int64_t)(c < 0 ? c + W : (c >= W ? (c == W ? 0 : W - 1) : c)) * C;
+    };
+    auto load_row = [&](const bf16 *column, int y, Row &r) {
+        const bf16 *q = column + (int64_t)y * W * C;
+        r.h[0] = *reinterpret_cast<const bf16x8 *>(q);
+        r.h[1] = *reinterpret_cast<const bf16x8 *>(q + 16);
+    };
     for (int64_t n = (int64_t)blockIdx.x * 2 + sub; n < nunits; n += (int64_t)gridDim.x * 2) {
         const Unit u = unit_of(n, TX, tiles_x, chunks, ru, H);
-        const int x = u.x0 + j;
-        const bool ok = x < W;
-        const int c = x + dx - 1;
-        const bf16 *gp = ga + u.b * HW * C + (int64_t)(ok ? x : W - 1) * C + kh * 8;
-        const bf16 *xp = xa + plane_shift(u.b, nz, dzo) * HW * C + kh * 8 +
-                         (int64_t)(c < 0 ? c + W : (c >= W ? (c == W ? 0 : W - 1) : c)) * C;
-        auto load_g = [&](int y, Row &r) {  // rows past the unit are loaded again and not used
-            const bf16 *q = gp + (int64_t)min(y, u.yb - 1) * W * C;
-            r.h[0] = *reinterpret_cast<const bf16x8 *>(q);
-            r.h[1] = *reinterpret_cast<const bf16x8 *>(q + 16);
-        };
-        auto load_x = [&](int y, Row &r) {
-            const bf16 *q = xp + (int64_t)wrap(min(y, u.yb), H) * W * C;
-            r.h[0] = *reinterpret_cast<const bf16x8 *>(q);
-            r.h[1] = *reinterpret_cast<const bf16x8 *>(q + 16);
-        };
+        const bool ok = u.x0 + j < W;
+        const bf16 *gp = g_column(u), *xp = x_column(u);
+        auto load_g = [&](int y, Row &r) { load_row(gp, min(y, u.yb - 1), r); };  // rows past the unit are loaded again and not used
+        auto load_x = [&](int y, Row &r) { load_row(xp, wrap(min(y, u.yb), H), r); };
         // step r: input row r against the gradient rows r + 1 (dy = 0), r (1)
         // and r - 1 (2); two rows of loads in flight
         bf16x8 G0[2], G1[2], G2[2];
@@ -1203,7 +1205,58 @@ __global__ __launch_bounds__(WGT, 3) void k_wgrad_mid(const bf16 *xa, const bf16
             if (r + 1 <= u.yb) step(r + 1, ga_[1], xa_[1]);
         }
     }
+    // An infinity or NaN in one channel of a point comes back from the
+    // transpose as NaN in all 32 (0 times it), and any of the sums is NaN then:
+    // the sums are taken again, the transposes through LDS.
+    bool nan = db != db;
+#pragma unroll
+    for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) nan = nan || acc[dy][v] != acc[dy][v];
+    if (__any(nan)) {
+        bf16 *stage = reinterpret_cast<bf16 *>(wgrad_lds) + wave * TX * C;  // this wave's: [point][channel]
+        auto transpose_lds = [&](const Row &r, bf16x8 (&o)[2]) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) *reinterpret_cast<bf16x8 *>(stage + j * C + 16 * h + 8 * kh) = r.h[h];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o[v >> 3][v & 7] = stage[(8 * (v >> 2) + 4 * kh + (v & 3)) * C + j];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        };
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy) acc[dy] = f32x16{};
+        db = 0.0f;
+        for (int64_t n = (int64_t)blockIdx.x * 2 + sub; n < nunits; n += (int64_t)gridDim.x * 2) {
+            const Unit u = unit_of(n, TX, tiles_x, chunks, ru, H);
+            const bool ok = u.x0 + j < W;
+            const bf16 *gp = g_column(u), *xp = x_column(u);
+#pragma unroll 1
+            for (int r = u.ya - 1; r <= u.yb; ++r) {
+                Row row;
+                bf16x8 X[2], G[2];
+                load_row(xp, wrap(r, H), row);
+                if (!ok) row.h[0] = row.h[1] = zero;
+                transpose_lds(row, X);
+#pragma unroll
+                for (int dy = 0; dy < 3; ++dy) {
+                    const int y = r + 1 - dy;
+                    if (y < u.ya || y >= u.yb) continue;
+                    load_row(gp, y, row);
+                    if (!ok) row.h[0] = row.h[1] = zero;
+                    transpose_lds(row, G);
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        acc[dy] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(G[q], X[q], acc[dy], 0, 0, 0);
+                        if (dy == 1)
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) db += (float)G[q][e];
+                    }
+                }
+            }
+        }
+    }
     db += __shfl_xor(db, 32, 64);
+    __syncthreads();  // no wave stages in `red` any more
     for (int i = tid; i < NWL; i += WGT) red[i] = 0.0f;
     __syncthreads();
     for (int sv = 0; sv < 2; ++sv) {  // the three shifts of a unit write different taps
