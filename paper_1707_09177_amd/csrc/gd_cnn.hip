@@ -332,12 +332,12 @@ __device__ __forceinline__ Piece tile_piece(int k, int x0, int y0, int H, int W)
     gx = gx < 0 ? gx + W : (gx >= W ? (gx == W ? 0 : W - 1) : gx);
     return {(uint32_t)gy * (uint32_t)W + (uint32_t)gx, (uint32_t)c};
 }
-// start the load of piece k into LDS
-__device__ __forceinline__ void stage_piece(const bf16 *plane, unsigned char *tile, int k, Piece at, int wave) {
+// start the load of piece k, `at` elements into the plane, into LDS
+__device__ __forceinline__ void stage_piece(const bf16 *plane, unsigned char *tile, int k, uint64_t at, int wave) {
     if ((k + 1) * 256 <= CH || k * 256 + (int)threadIdx.x < CH)
-        __builtin_amdgcn_global_load_lds(
-            (const __attribute__((address_space(1))) void *)(plane + (uint64_t)at.point * C + at.chunk * 8),
-            (__attribute__((address_space(3))) void *)(tile + (k * 256 + wave * 64) * 16), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(plane + at),
+                                         (__attribute__((address_space(3))) void *)(tile + (k * 256 + wave * 64) * 16), 16,
+                                         0, 0);
 }
 // wait for this wave's outstanding loads (vmcnt 0), tile loads included
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
@@ -453,7 +453,10 @@ __global__ __launch_bounds__(256, 3) void k_conv_mid(const bf16 *in, const bf16 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int j = lane & 31, kh = lane >> 5;
 #pragma unroll 1
-    for (int k = 0; k < CPL; ++k) stage_piece(in + pz * H * W * C, conv_tile, k, tile_piece(k, x0, y0, H, W), wave);
+    for (int k = 0; k < CPL; ++k) {
+        const Piece p = tile_piece(k, x0, y0, H, W);
+        stage_piece(in + pz * H * W * C, conv_tile, k, (uint64_t)p.point * C + p.chunk * 8, wave);
+    }
     bf16x8 Wf[K / 16];
 #pragma unroll
     for (int ks = 0; ks < K / 16; ++ks) Wf[ks] = *reinterpret_cast<const bf16x8 *>(wmat + j * K + ks * 16 + kh * 8);
@@ -484,7 +487,9 @@ __global__ __launch_bounds__(256, 3) void k_conv_mid(const bf16 *in, const bf16 
 // bf16 matrix product reaches on this card).  All three planes' tiles in LDS
 // per output plane, the weights loaded per plane and every operand read from
 // LDS for each output row took 1387 us.
-template <int MODE>
+// WIDE: for planes of more than 2^30 points, whose pieces' places do not fit 32
+// bits (32-bit places for the others: forward 4 x 128^3 2181 -> 2160 us)
+template <int MODE, bool WIDE>
 __global__ __launch_bounds__(256, 1) void k_conv_mid3(const bf16 *in, const bf16 *slices, const float *bias,
                                                       const bf16 *mask, bf16 *out, int H, int W, int nz, int tiles_x,
                                                       int tiles_y, int zruns, int zrun) {
@@ -499,19 +504,21 @@ __global__ __launch_bounds__(256, 1) void k_conv_mid3(const bf16 *in, const bf16
     const int j = lane & 31, kh = lane >> 5;
     constexpr size_t TB = kConvLds;
     // plane z (periodic) into ring slot (z - zlo + 1) mod 4
-    uint32_t point[CPL], chunks = 0;  // the pieces' points, and two bits of chunk each
+    // the pieces' places; WIDE: their points, and two bits of chunk each
+    uint32_t piece[CPL], chunks = 0;
     static_assert(CPL <= 16);
 #pragma unroll
     for (int k = 0; k < CPL; ++k) {
         const Piece p = tile_piece(k, x0, y0, H, W);
-        point[k] = p.point;
+        piece[k] = WIDE ? p.point : p.point * 4 + p.chunk;
         chunks |= p.chunk << 2 * k;
     }
     auto stage = [&](int z) {
         const bf16 *plane = in + (p0 + wrap(z, nz)) * HW * C;
 #pragma unroll
         for (int k = 0; k < CPL; ++k)
-            stage_piece(plane, conv_tile + (size_t)((z - zlo + 1) & 3) * TB, k, {point[k], chunks >> 2 * k & 3}, wave);
+            stage_piece(plane, conv_tile + (size_t)((z - zlo + 1) & 3) * TB, k,
+                        WIDE ? (uint64_t)piece[k] * C + (chunks >> 2 * k & 3) * 8 : (uint64_t)piece[k] * 8, wave);
     };
     stage(zlo - 1);
     stage(zlo);
@@ -1208,12 +1215,12 @@ __global__ __launch_bounds__(WGT, 3) void k_wgrad_mid(const bf16 *xa, const bf16
     // An infinity or NaN in one channel of a point comes back from the
     // transpose as NaN in all 32 (0 times it), and any of the sums is NaN then:
     // the sums are taken again, the transposes through LDS.
-    bool nan = db != db;
+    float zeros[4] = {db * 0.0f, 0.0f, 0.0f, 0.0f};  // 0, or NaN from an infinity or NaN
 #pragma unroll
-    for (int dy = 0; dy < 3; ++dy)
+    for (int v = 0; v < 16; ++v)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) nan = nan || acc[dy][v] != acc[dy][v];
-    if (__any(nan)) {
+        for (int dy = 0; dy < 3; ++dy) zeros[dy + 1] = __builtin_fmaf(acc[dy][v], 0.0f, zeros[dy + 1]);
+    if (__any(!(zeros[0] + zeros[1] + zeros[2] + zeros[3] == 0.0f))) {
         bf16 *stage = reinterpret_cast<bf16 *>(wgrad_lds) + wave * TX * C;  // this wave's: [point][channel]
         auto transpose_lds = [&](const Row &r, bf16x8 (&o)[2]) {
 #pragma unroll
@@ -1494,7 +1501,8 @@ int launch_mid3(const gd_grid *g, const bf16 *in, const bf16 *slices, const floa
     const int zruns = (nz + zrun - 1) / zrun;
     const int64_t blk = cols * zruns;
     if (blk > 0x7fffffff) return fail(GD_EINVAL, "field too large");
-    auto kern = k_conv_mid3<MODE>;
+    const bool wide = (int64_t)H * W > int64_t(1) << 30;
+    const auto kern = wide ? k_conv_mid3<MODE, true> : k_conv_mid3<MODE, false>;
     GD_LAUNCH(kern, dim3((unsigned)blk), dim3(256), 4 * kConvLds, st, in, slices, bias, mask, out, H, W, nz,
               tiles_x, tiles_y, zruns, zrun);
     return GD_OK;
