@@ -90,16 +90,16 @@ __device__ __forceinline__ double ghat(const Fold &f, int a, int b, int c) {
     return 1.0 / (1.0 + k2 * f.inv_kc2);
 }
 
-// |coefficient|^2 summed over the signs of k_y and k_z at (kx, |ky|, |kz|)
+// |scale coefficient|^2 summed over the signs of k_y and k_z at (kx, |ky|, |kz|)
 template <typename T>
-__device__ __forceinline__ double power(const Fold &f, const T *F, int kx, int ky, int kz) {
+__device__ __forceinline__ double power(const Fold &f, const T *F, double scale, int kx, int ky, int kz) {
     double s = 0.0;
     const int ys = (ky == 0 || 2 * ky == f.ny) ? 1 : 2, zs = (kz == 0 || 2 * kz == f.nz) ? 1 : 2;
     for (int zi = 0; zi < zs; ++zi)
         for (int yi = 0; yi < ys; ++yi) {
             const int64_t row = (int64_t)(zi ? f.nz - kz : kz) * f.ny + (yi ? f.ny - ky : ky);
             const T *p = F + row * f.nxs + 2 * kx;
-            const double re = (double)p[0], im = (double)p[1];
+            const double re = scale * (double)p[0], im = scale * (double)p[1];
             s += re * re + im * im;
         }
     return s;
@@ -151,19 +151,30 @@ __global__ __launch_bounds__(256) void k_fold(const T *X, Params P) {
     }
     const int64_t fld = blockIdx.y;
     const T *F = X + fld * f.field;
-    double s = power(f, F, a, b, c);
-    if (f.kind == FOLD_SQUARE) {
-        if (a != b) s += power(f, F, b, a, 0);
-    } else if (f.kind == FOLD_CUBE) {
-        // the distinct permutations of (a, b, c), a >= b >= c
-        if (b != c) s += power(f, F, a, c, b);
-        if (a != b) s += power(f, F, b, a, c);
-        if (a != b && b != c) s += power(f, F, b, c, a) + power(f, F, c, a, b) + power(f, F, c, b, a);
-        if (a != b && b == c) s += power(f, F, b, b, a);
-        if (a == b && b != c) s += power(f, F, c, a, b);
+    // FP64 coefficients whose squares leave the range (a class's part in the
+    // solve's sums may still be in it: the mean has no residual) are summed again
+    double s, scale = 1.0, unscale = 1.0;
+#pragma unroll 1
+    for (;;) {
+        auto at = [&](int kx, int ky, int kz) { return power(f, F, scale, kx, ky, kz); };
+        s = at(a, b, c);
+        if (f.kind == FOLD_SQUARE) {
+            if (a != b) s += at(b, a, 0);
+        } else if (f.kind == FOLD_CUBE) {
+            // the distinct permutations of (a, b, c), a >= b >= c
+            if (b != c) s += at(a, c, b);
+            if (a != b) s += at(b, a, c);
+            if (a != b && b != c) s += at(b, c, a) + at(c, a, b) + at(c, b, a);
+            if (a != b && b == c) s += at(b, b, a);
+            if (a == b && b != c) s += at(c, a, b);
+        }
+        if (sizeof(T) == 4 || scale != 1.0 || (s >= 0x1p-900 && s <= 0x1p900)) break;
+        const bool small = s < 1.0;
+        scale = small ? 0x1p600 : 0x1p-600;
+        unscale = small ? 0x1p-600 : 0x1p600;
     }
     const int64_t j = class_of(f, a, b, c);
-    P.x[fld * f.K + j] = sqrt(s);
+    P.x[fld * f.K + j] = unscale * sqrt(s);
     if (fld == 0) P.lam[j] = ghat(f, a, b, c);
 }
 
@@ -349,13 +360,14 @@ __global__ __launch_bounds__(kThreads) void k_red_solve(Params P) {
                 }
             }
         }
-        // the factors u_j / x_j; a class without content keeps the start's
+        // the factors u_j / x_j; a class without content, and every class of a
+        // field that did not finish a pass (it may not be finite), keeps the start's
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int64_t j = j0 + (int64_t)e * kThreads;
             if (j < K) {
                 const double xv = x[j];
-                x[j] = xv == 0.0 ? (P.init == GD_INIT_UBAR ? 1.0 : 0.0) : u[e] / xv;
+                x[j] = iters == 0 || xv == 0.0 ? (P.init == GD_INIT_UBAR ? 1.0 : 0.0) : u[e] / xv;
             }
         }
         if (wg == 0 && threadIdx.x == 0) {
@@ -400,8 +412,10 @@ __global__ __launch_bounds__(kExpand) void k_expand(const T *UB, T *U, Params P)
             const int a = kx, b = min(ky, (int)f.ny - ky), c = min(kz, (int)f.nz - kz);
             const V2 v = B[i];
             const double m = fac[class_of(f, a, b, c)], g = ghat(f, a, b, c);
-            o[0] = T(m * (double)v[0]);
-            o[1] = T(m * (double)v[1]);
+            if (m != 0.0) {  // 0 is 0 for coefficients that are not finite too
+                o[0] = T(m * (double)v[0]);
+                o[1] = T(m * (double)v[1]);
+            }
             const double d0 = (double)v[0] - g * (double)o[0], d1 = (double)v[1] - g * (double)o[1];
             acc += d0 * d0 + d1 * d1;
         }
