@@ -582,27 +582,22 @@ __global__ __launch_bounds__(kThreads) void k_resident(Params P) {
         if (!ok) break;
         points_do([&](int k, int j, int g) { __builtin_nontemporal_store(u[k][j], uo + g); });
         if (wg == 0 && tid == 0) {
-            gd_info out;
-            out.iters = iters;
-            out.status = status;
-            out.r_ref = r_ref;
-            out.r0 = r0;
-            out.r_final = sqrt(rr);
-            out.r_true = r_true;
-            out.start = start;
-            out.replaced = nrep;
-            // no part of the record stays in this L2: another workgroup may write its status
-            static_assert(sizeof(gd_info) == 6 * sizeof(uint64_t));
-            uint64_t rec[6];
-            __builtin_memcpy(rec, &out, sizeof out);
-#pragma unroll
-            for (int k = 0; k < 6; ++k) st_agent(reinterpret_cast<uint64_t *>(P.info + fld) + k, rec[k]);
+            gd_info *out = P.info + fld;
+            out->iters = iters;
+            // not left in this L2: the mark below may come from another one
+            st_agent(&out->status, (int32_t)status);
+            out->r_ref = r_ref;
+            out->r0 = r0;
+            out->r_final = sqrt(rr);
+            out->r_true = r_true;
+            out->start = start;
+            out->replaced = nrep;
         }
     }
     if (!ok && wg == 0 && tid == 0)
         for (; fld < P.batch; fld += P.nclusters) {
             st_agent(&P.info[fld].status, (int32_t)GD_TIMEOUT);
-            st_agent(&P.info[fld].iters, 0);
+            P.info[fld].iters = 0;
         }
     // A workgroup gives up by itself, so after a reduction some may have gone
     // on and others not: workgroup 0 may have written the record of a field
