@@ -271,9 +271,11 @@ typedef struct gd_tune_info {
                                 as many as keep every resident wave busy.
                                 Uniform solves only (uneven batches ignore
                                 it); the tuner tries it for 3D fields. */
-    int32_t resident;        /* 1: the field is solved in the chip's registers,
-                                where the choices above do not apply (fields
-                                too large for it use them) */
+    int32_t resident;        /* 1: the field is solved in the chip's registers
+                                if it fits them, and the choices above do not
+                                apply; 0: it is streamed.  (Untuned solves
+                                take the one expected to be faster for the
+                                field and the batch.) */
     double best_ms;          /* trial time of the chosen configuration (the
                                 leaders' round: solves of 8 Krylov or 20 Van
                                 Cittert / steepest-descent passes) */

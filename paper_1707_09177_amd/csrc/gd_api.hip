@@ -451,6 +451,16 @@ TuneCfg untuned(int ndim, bool spec) {
     return c;
 }
 
+// The plan of a uniform solve in registers; res: kResWhereFits or kResRule
+bool resident_plan(int solver, const gd_grid *g, int ncu, int res, gdres::Plan *plan) {
+    const int64_t nx = g->n[0], ny = g->n[1], nz = g->ndim == 3 ? g->n[2] : 1;
+    const int tsize = g->dtype == GD_F32 ? 4 : 8;
+    const size_t field_bytes = (size_t)g->batch * (size_t)grid_points(g) * tsize;
+    return gdres::plan(solver, g->ndim, nx, ny, nz, tsize, g->batch, ncu, plan) &&
+           gdres::scratch_ok(*plan, g->batch, ncu, field_bytes, (size_t)nvec_of(solver) * align_up(field_bytes, 256)) &&
+           (res == kResWhereFits || gdres::faster(solver, g->ndim, nx, ny, nz, tsize, g->batch, ncu, *plan));
+}
+
 int solve_uniform(int solver, const gd_grid *g, const void *ubar, void *u, const gd_opts *o, void *work,
                   size_t work_bytes, gd_info *info, void *stream, const TuneCfg *force, const SpecParams *spec,
                   UniStage stage, UniView *view) {
@@ -491,19 +501,18 @@ int solve_uniform(int solver, const gd_grid *g, const void *ubar, void *u, const
     else tune_lookup(key_uniform(solver, g, aligned) + (spec ? ":spec" : ""), &cfg);
     // A field whose vectors fit the chip's registers is solved there: a pass
     // costs its reductions and boundary exchanges instead of 4 to 15 field
-    // accesses and a grid barrier per sweep (gd_resident_kernel.h).  Not while
+    // accesses and a grid barrier per sweep (gd_resident_kernel.h), unless the
+    // batch fills the boxes so badly that streaming is faster.  Not while
     // barrier timestamps are recorded or GD_STEAL pins the tile schedule.
-    if (stage == UNI_ALL && !spec && cfg.res && !g_trace && !getenv("GD_STEAL")) {
+    if (stage == UNI_ALL && !spec && cfg.res != kResNever && !g_trace && !getenv("GD_STEAL")) {
         DevProps dp;
         if ((rc = dev_props(&dp))) return rc;
         gdres::Plan plan;
-        const size_t vec_total = (size_t)nvec_of(solver) * vec_bytes;
-        if (gdres::plan(solver, g->ndim, nx, ny, nz, (int)tsize, dp.ncu, &plan) &&
-            gdres::scratch_ok(plan, g->batch, dp.ncu, field_bytes, vec_total)) {
+        if (resident_plan(solver, g, dp.ncu, cfg.res, &plan)) {
             const int64_t ticks = wait_ticks_of(o);
             return gdres::solve(solver, g, plan, grid_weight(g), ubar, u, o, replacements_of(o),
                                 ticks > 0 ? ticks : (int64_t)10 * 1000 * dp.wall_khz, dp.ncu, (char *)work + off_vec,
-                                field_bytes, vec_total, info, (hipStream_t)stream);
+                                field_bytes, (size_t)nvec_of(solver) * vec_bytes, info, (hipStream_t)stream);
         }
     }
     TileShape ts = choose_tiles(g->ndim, nx, ny, nz, g->batch, (int)tsize, aligned, solver, false);
@@ -952,8 +961,21 @@ int tune_uniform(int solver, const gd_grid *g, const void *ubar, void *u, void *
     if (rc) return rc;
     if (solver < GD_VANCITTERT || solver > GD_STEEPEST_DESCENT) return fail(GD_EINVAL, "bad solver %d", solver);
     const gd_opts o = trial_opts(solver), o2 = trial_opts(solver, true);
-    // the untuned default, then the tile schedules of the streaming kernel
+    // the untuned default, the solve in registers where it is not the default,
+    // then the tile schedules of the streaming kernel
     std::vector<TuneCfg> cands(1, untuned(g->ndim, spec != nullptr));
+    cands[0].res = kResNever;
+    if (!spec) {
+        DevProps dp;
+        if ((rc = dev_props(&dp))) return rc;
+        gdres::Plan plan;
+        if (resident_plan(solver, g, dp.ncu, kResRule, &plan)) {
+            cands[0].res = kResWhereFits;
+        } else if (resident_plan(solver, g, dp.ncu, kResWhereFits, &plan)) {
+            cands.push_back(cands[0]);
+            cands[1].res = kResWhereFits;
+        }
+    }
     std::vector<int> rows = {0};
     if (g->ndim == 3 && !spec) rows = {0, 1, 2, 4};
     for (int bp : kBpcCands)
@@ -963,7 +985,7 @@ int tune_uniform(int solver, const gd_grid *g, const void *ubar, void *u, void *
                     for (int il = 0; il < 2; ++il)
                         for (int wc = 0; wc < 2; ++wc) {
                             TuneCfg c;
-                            c.res = 0;
+                            c.res = kResNever;
                             c.tpw = t;
                             c.rows = r;
                             c.tail = tl;
@@ -981,7 +1003,7 @@ int tune_uniform(int solver, const gd_grid *g, const void *ubar, void *u, void *
             for (int r : rows)
                 for (int sg = 1; sg <= 4; ++sg) {
                     TuneCfg c;
-                    c.res = 0;
+                    c.res = kResNever;
                     c.tpw = 1;
                     c.rows = r;
                     c.tail = 0;
@@ -1178,7 +1200,7 @@ int gd_tune_set(int32_t solver, const gd_grid *g, const void *ubar, const void *
     if (solver < GD_VANCITTERT || solver > GD_STEEPEST_DESCENT) return fail(GD_EINVAL, "bad solver %d", solver);
     TuneCfg cfg;
     if ((rc = tune_choice(choice, &cfg))) return rc;
-    cfg.res = choice->resident != 0;
+    cfg.res = choice->resident == 1 ? kResWhereFits : kResNever;
     const bool aligned = ((uintptr_t)ubar % 16 == 0) && ((uintptr_t)u % 16 == 0);
     tune_store(key_uniform(solver, g, aligned), cfg);
     return GD_OK;

@@ -176,6 +176,7 @@ struct Params {
 // resident wave (tile granularity) and, for 3D fields in the uniform kernels,
 // rows per tile (0 = the default rule) and tiles per column along the march
 // axis (0 = the wave-count rule).
+constexpr int kResNever = 0, kResWhereFits = 1, kResRule = 2;  // kResRule: where that is expected to be faster
 struct TuneCfg {
     int tpw = kTilesPerWave;
     int rows = 0;
@@ -184,7 +185,7 @@ struct TuneCfg {
     int wc = 0;   // per-wave tile claims
     int bpc = kBlocksPerCu;  // workgroups per CU (0: as many as fit)
     int segs = 0;  // > 0: every column is cut into this many long tiles, whatever the wave count
-    int res = 1;   // a field that fits the chip's registers is solved there (the rest does not apply then)
+    int res = kResRule;  // whether a field that fits the chip's registers is solved there (the rest does not apply then)
 };
 
 // A solve on a stored Fourier spectrum (the differential filter); hw is the

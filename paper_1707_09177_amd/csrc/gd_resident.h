@@ -19,10 +19,12 @@ struct Plan {
     size_t lds;          // bytes of the box with its halo
 };
 
-// The plan for one field, or false where the streaming solver takes it: a row
-// is longer than the threads can hold, a box of one row does not fit LDS, or
-// the field needs more boxes than the GPU has CUs.
-bool plan(int solver, int ndim, int64_t nx, int64_t ny, int64_t nz, int tsize, int ncu, Plan *p);
+// The plan for a batch of one grid, or false where only the streaming solver
+// can take it: a row is longer than the threads can hold, a box of one row does
+// not fit LDS, or the field needs more boxes than the GPU has CUs.
+bool plan(int solver, int ndim, int64_t nx, int64_t ny, int64_t nz, int tsize, int64_t batch, int ncu, Plan *p);
+// whether the plan is expected to be no slower than the streaming solver
+bool faster(int solver, int ndim, int64_t nx, int64_t ny, int64_t nz, int tsize, int64_t batch, int ncu, const Plan &p);
 
 // scratch: vec_bytes of the caller's workspace, first `field_bytes` of them the exchange buffer
 int solve(int solver, const gd_grid *g, const Plan &p, double hw, const void *ubar, void *u, const gd_opts *o,

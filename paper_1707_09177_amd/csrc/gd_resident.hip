@@ -30,11 +30,70 @@ const void *kernel_of(int dtype, int ndim, int solver, const Plan &p) {
     return ndim == 2 ? kernels_f64_2d(solver, p) : kernels_f64_3d(solver, p);
 }
 
-bool plan(int solver, int ndim, int64_t nx, int64_t ny, int64_t nz, int tsize, int ncu, Plan *p) {
+// ---- the rule: resident or streamed, and in which boxes
+//
+// A batch is solved in rounds of as many fields as fit the CUs at once, and a
+// round's time depends on the points per thread and the exchanges, not on how
+// full the boxes are.  So fields that fill their boxes badly, or leave CUs
+// without a field, lose against the streaming solver in large batches (10
+// passes, resident and streamed: 8 x 160^3 FP32 Van Cittert, 189 boxes, one field
+// at a time, 2525 and 1545 us; 51 x 623 x 1240 FP64 steepest descent, 156 boxes,
+// 6130 and 5017), and small fields in short columns against the same fields in
+// full ones (1312 x 15 x 24 x 45 FP64 Van Cittert, 8 boxes and 4, 3212 and 1948).
+// Both times are estimated from the tables below (us, 256 CUs) for solves of
+// kPasses passes.  Of 670 timed solves of random shapes and batches (300 to 6 M
+// points per field, up to 48 M in all) five took more than 1.1 times the better
+// choice's time.
+
+constexpr double kPasses = 8;
+// A pass of a round of fields of 17 to 64 (2D) or 65 to 128 boxes (3D), by points
+// per thread (4, 8, 16, and 12 or 24), and a round's start and end
+constexpr double kPass[4][2][4] = {{{4.9, 6.1, 7.2, 0}, {7, 10, 12, 21}},               // Van Cittert, 2D and 3D
+                                   {{7.1, 9.7, 10.5, 17.5}, {10.1, 15, 17.9, 27}},      // CG
+                                   {{13.5, 18.5, 24, 0}, {18.9, 27.5, 34.5, 0}},        // BiCGSTAB
+                                   {{7, 8.4, 9.7, 0}, {10.1, 14.5, 17.3, 27}}};         // steepest descent
+constexpr double kEnds[2][4] = {{17, 23, 28, 70}, {20, 32, 44, 105}};
+
+int64_t fields_at_once(const Plan &p, int ncu) {
+    const int64_t cap = std::min<int64_t>(ncu, gdcl::kMaxW);
+    return p.W == 1 ? ncu : cap / p.W;
+}
+
+double resident_us(int solver, int ndim, const Plan &p, int64_t batch, int ncu) {
+    const int points = p.kc * p.kz, by = points == 4 ? 0 : points == 8 ? 1 : points == 16 ? 2 : 3;
+    const int64_t at_once = fields_at_once(p, ncu), rounds = (batch + at_once - 1) / at_once;
+    // one box exchanges nothing; more boxes are more words to collect and, in 3D, more neighbours elsewhere
+    // (2D boxes of four long rows: more of a box is boundary)
+    const double rows = p.kc * p.kz == 8 && p.kc == 2 ? 1.2 : 1.0;
+    const double share = ndim == 2 ? rows * (p.W == 1 ? 0.42 : p.W <= 16 ? 0.95 : p.W <= 64 ? 1.0 : 1.05)
+                                   : (p.W == 1 ? 0.38 : p.W <= 16 ? 0.73 : p.W <= 64 ? 0.9 : p.W <= 128 ? 1.0 : 1.08);
+    return (double)rounds * ((p.W == 1 ? 0.55 : share) * kEnds[ndim - 2][by] + kPasses * share * kPass[solver][ndim - 2][by]);
+}
+
+// The streaming solver: the field accesses at 4.1 TB/s or the waves' steps (a
+// row of a tile in 2D, four rows in 3D; ns, FP32 and FP64), and the grid barriers
+double streamed_us(int solver, int ndim, int64_t nx, int64_t ny, int64_t nz, int tsize, int64_t batch) {
+    // accesses as measured at that rate: 3D tiles read their halo rows again
+    constexpr double accesses[2][4][2] = {{{4, 4}, {8, 7.4}, {14, 14}, {6, 5.2}},
+                                          {{5.2, 4.5}, {9.5, 8.6}, {17, 15.5}, {7.5, 6.2}}};
+    constexpr double barriers[4] = {17, 34, 51, 34};
+    constexpr double step[4][2][2] = {
+        {{0.45, 0.52}, {0.86, 1.0}}, {{0.85, 1.05}, {1.72, 2.25}}, {{1.35, 1.9}, {4.0, 5.3}}, {{0.73, 0.83}, {1.5, 1.65}}};
+    const int64_t lanes = 64 * (nx % (16 / tsize) == 0 ? 16 / tsize : 1), segs = (nx + lanes - 1) / lanes;
+    const double b = (double)batch, rows = (double)(ndim == 2 ? ny : nz), halo = 1.0 + 2.0 / rows;
+    const double steps = b * (double)segs * rows * halo * (double)(ndim == 2 ? 1 : ny >= 4 ? (ny + 3) / 4 : ny);
+    const double bytes = b * (double)(nx * ny * nz) * tsize * accesses[ndim - 2][solver][tsize == 8];
+    return (kPasses + 1.5) * (std::max(bytes / 4.1e6, steps * step[solver][ndim - 2][tsize == 8] * 1e-3) + barriers[solver]);
+}
+
+bool faster(int solver, int ndim, int64_t nx, int64_t ny, int64_t nz, int tsize, int64_t batch, int ncu, const Plan &p) {
+    // streamed where it leads clearly: the streaming estimate leaves out how its tiles divide
+    return resident_us(solver, ndim, p, batch, ncu) * 0.78 <= streamed_us(solver, ndim, nx, ny, nz, tsize, batch);
+}
+
+bool plan(int solver, int ndim, int64_t nx, int64_t ny, int64_t nz, int tsize, int64_t batch, int ncu, Plan *p) {
     const int64_t cap = std::min<int64_t>(ncu, gdcl::kMaxW);
     if (nx > 2 * kThreads || nx * ny > int64_t(0x7fffffff) || nx * ny * nz > int64_t(0x7fffffff)) return false;
-    // The plan depends on the field alone, so a field's result does not
-    // depend on the batch it is solved in.
     const int kc = nx > kThreads ? 2 : 1;
     if (ndim == 3 && kc > 1) return false;
     auto shape = [&](int kz, bool f0_lds) {
@@ -61,12 +120,20 @@ bool plan(int solver, int ndim, int64_t nx, int64_t ny, int64_t nz, int tsize, i
         p->lds = lds(p->rows);
         return p->W <= cap;
     };
+    const int some = points(tsize) / kc, most = most_points(solver, ndim, tsize) / kc;
+    const bool full = (solver == GD_BICGSTAB && shape(some, true)) || shape(some, false) ||
+                      (most > some && shape(most, false));
     // Short columns while that leaves room for 16 fields at a time: a pass's
     // work within a workgroup then takes a quarter of the time, and the
-    // exchanges and reductions take the same.
-    const int some = points(tsize) / kc, most = most_points(solver, ndim, tsize) / kc;
-    return (kc == 1 && shape(kSmallZ, false) && p->W <= kSmallW) || (solver == GD_BICGSTAB && shape(some, true)) ||
-           shape(some, false) || (most > some && shape(most, false));
+    // exchanges and reductions take the same.  Not where a batch that does not
+    // fit at once takes so many more rounds then that full columns are faster.
+    const Plan whole = *p;
+    if (kc == 1 && shape(kSmallZ, false) && p->W <= kSmallW &&
+        (!full || batch <= fields_at_once(*p, ncu) ||
+         resident_us(solver, ndim, *p, batch, ncu) <= resident_us(solver, ndim, whole, batch, ncu)))
+        return true;
+    *p = whole;
+    return full;
 }
 
 struct Control {
@@ -75,7 +142,7 @@ struct Control {
 };
 Control control_of(const Plan &p, int64_t batch, int ncu) {
     Control c;
-    c.nclusters = p.W == 1 ? batch : std::min<int64_t>(batch, std::min<int64_t>(ncu, gdcl::kMaxW) / p.W);
+    c.nclusters = p.W == 1 ? batch : std::min<int64_t>(batch, fields_at_once(p, ncu));
     c.slot = 0;
     c.flag = gd::align_up((size_t)c.nclusters * 2 * p.W * gdcl::kWords * sizeof(uint64_t), 256);
     c.abort = c.flag + (size_t)c.nclusters * p.W * 128;
