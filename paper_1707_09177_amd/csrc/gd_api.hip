@@ -439,14 +439,26 @@ std::string key_uniform(int solver, const gd_grid *g, bool aligned) {
 // over 33 batches of 3.4 M to 67 M points (FP32 and FP64, odd sizes among
 // them), 5 BiCGSTAB passes against two tiles per wave, a 15 % tail and two
 // rows: 3 x 256^3 FP32 4.94 -> 3.97 ms, 1 x 256^3 3.05 -> 1.51, 2048^2 FP64 2.48
-// -> 1.35, 4 x 4096^2 FP32 5.27 -> 4.44; at worst 2 to 3 % slower (176^3 FP32,
-// Van Cittert on 3 x 256^3 FP64).
-TuneCfg untuned(int ndim, bool spec) {
+// -> 1.35, 4 x 4096^2 FP32 5.27 -> 4.44; over 128 more, all solvers, 0.80 of the
+// time (median), at worst 5 % slower (2 x 102 x 122 x 257 FP64 BiCGSTAB) but for
+// 2D batches of several fields with one value per lane (odd rows) that are
+// larger than the caches: there one tile for each wave takes up to 1.18 times as
+// long, and two per wave 0.72 to 0.93 of one (10 x 1851 x 3179 FP32 BiCGSTAB 9.84
+// -> 7.13 ms, 10 x 2730 x 1793 FP64 steepest descent 10.4 -> 8.0; with 13 to 23 M
+// points 0.80 to 1.40 of one).
+TuneCfg untuned(const gd_grid *g, bool aligned, bool spec, int ncu) {
     TuneCfg c;
-    if (!spec) {
-        c.tpw = 1;
-        c.tail = 0;
-        if (ndim == 3) c.rows = 4;
+    if (spec) return c;
+    c.tpw = 1;
+    c.tail = 0;
+    if (g->ndim == 3) {
+        c.rows = 4;
+    } else if (g->batch > 1 && g->batch * g->n[0] * g->n[1] >= int64_t(24) << 20) {
+        const TileShape ts = choose_tiles(2, g->n[0], g->n[1], 1, g->batch, g->dtype == GD_F32 ? 4 : 8, aligned, -1, false);
+        const int64_t waves = (int64_t)kBlocksPerCu * ncu * WPB;
+        const int64_t cols = g->batch * tiles_per_plane(2, g->n[0], g->n[1], ts.vw, ts.R);
+        const int64_t L = balanced_L(g->n[1], cols, waves);
+        if (ts.vw == 1 && cols * ((g->n[1] + L - 1) / L) <= waves) c.tpw = 2;
     }
     return c;
 }
@@ -496,7 +508,9 @@ int solve_uniform(int solver, const gd_grid *g, const void *ubar, void *u, const
         if (stage == UNI_VIEW) return GD_OK;
     }
     const bool aligned = ((uintptr_t)ubar % 16 == 0) && ((uintptr_t)u % 16 == 0);
-    TuneCfg cfg = untuned(g->ndim, spec != nullptr);
+    DevProps dp;
+    if ((rc = dev_props(&dp))) return rc;
+    TuneCfg cfg = untuned(g, aligned, spec != nullptr, dp.ncu);
     if (force) cfg = *force;
     else tune_lookup(key_uniform(solver, g, aligned) + (spec ? ":spec" : ""), &cfg);
     // A field whose vectors fit the chip's registers is solved there: a pass
@@ -505,8 +519,6 @@ int solve_uniform(int solver, const gd_grid *g, const void *ubar, void *u, const
     // batch fills the boxes so badly that streaming is faster.  Not while
     // barrier timestamps are recorded or GD_STEAL pins the tile schedule.
     if (stage == UNI_ALL && !spec && cfg.res != kResNever && !g_trace && !getenv("GD_STEAL")) {
-        DevProps dp;
-        if ((rc = dev_props(&dp))) return rc;
         gdres::Plan plan;
         if (resident_plan(solver, g, dp.ncu, cfg.res, &plan)) {
             const int64_t ticks = wait_ticks_of(o);
@@ -963,11 +975,12 @@ int tune_uniform(int solver, const gd_grid *g, const void *ubar, void *u, void *
     const gd_opts o = trial_opts(solver), o2 = trial_opts(solver, true);
     // the untuned default, the solve in registers where it is not the default,
     // then the tile schedules of the streaming kernel
-    std::vector<TuneCfg> cands(1, untuned(g->ndim, spec != nullptr));
+    const bool aligned = ((uintptr_t)ubar % 16 == 0) && ((uintptr_t)u % 16 == 0);
+    DevProps dp;
+    if ((rc = dev_props(&dp))) return rc;
+    std::vector<TuneCfg> cands(1, untuned(g, aligned, spec != nullptr, dp.ncu));
     cands[0].res = kResNever;
     if (!spec) {
-        DevProps dp;
-        if ((rc = dev_props(&dp))) return rc;
         gdres::Plan plan;
         if (resident_plan(solver, g, dp.ncu, kResRule, &plan)) {
             cands[0].res = kResWhereFits;
@@ -1018,7 +1031,6 @@ int tune_uniform(int solver, const gd_grid *g, const void *ubar, void *u, void *
     };
     const int best = time_candidates(cands, launch, (hipStream_t)stream, out);
     if (best < 0) return best;
-    const bool aligned = ((uintptr_t)ubar % 16 == 0) && ((uintptr_t)u % 16 == 0);
     tune_store(key_uniform(solver, g, aligned) + (spec ? ":spec" : ""), cands[best]);
     return GD_OK;
 }
