@@ -463,7 +463,7 @@ def germano_inputs(w, torch, gd, dev):
     return u, ubar
 
 
-def germano_result(gd, torch, ubar, w, s, steps, warmup, tune, dev):
+def germano_result(gd, torch, ubar, w, s, steps, warmup, dev):
     """One solver with the differential filter, whole call (forward FFT, solve
     on the coefficients, inverse FFT) to the workload's tolerance: time,
     passes, and the call's algorithmic bytes per second."""
@@ -472,7 +472,6 @@ def germano_result(gd, torch, ubar, w, s, steps, warmup, tune, dev):
     stream = torch.cuda.current_stream()
     d = gd.GermanoDeconvolver(ubar.shape, nd, ubar.dtype, s, gamma, device=dev)
     out = torch.empty_like(ubar)
-    tuned = d.autotune(ubar, out) if tune else None   # untimed
     reps = steps if s == "bicgstab" else max(2, steps // (10 if s in ("vc", "sd") else 2))
     for _ in range(warmup):
         d.solve(ubar, 5000, tol, out=out)
@@ -501,7 +500,7 @@ def germano_result(gd, torch, ubar, w, s, steps, warmup, tune, dev):
                 worst_true_rel_residual=max(i["r_true"] / i["r_ref"] for i in info),
                 points_per_s=npts / (ms * 1e-3), solve_kernel_bytes=algo, call_bytes=call_bytes,
                 call_GBs=call_bytes / (ms * 1e-3) / 1e9, call_hbm_frac=call_bytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                launch=launch, tune=tuned)
+                launch=launch)
 
 
 def main_germano(args, w, torch, gd, dev):
@@ -511,12 +510,9 @@ def main_germano(args, w, torch, gd, dev):
     u, ubar = germano_inputs(w, torch, gd, dev)
     npts = int(ubar.numel())
     stream = torch.cuda.current_stream()
-    if args.tune_only:
-        for s in args.solvers.split(","):
-            d = gd.GermanoDeconvolver(ubar.shape, nd, ubar.dtype, s, gamma, device=dev)
-            print(json.dumps({"solver": s, "tune": d.autotune(ubar)}))
+    if args.tune_only:   # solves from ubar run on wavenumber classes: nothing is tuned
         return
-    results = {s: germano_result(gd, torch, ubar, w, s, args.steps, args.warmup, not args.no_tune, dev)
+    results = {s: germano_result(gd, torch, ubar, w, s, args.steps, args.warmup, dev)
                for s in args.solvers.split(",")}
     # the paper's spectral assessment (its N = 5 comparison): the highest shell up to
     # which the recovered energy spectrum keeps at least half of the true one
@@ -1116,7 +1112,7 @@ def extra_germano(args, w, torch, gd, dev):
     """BiCGSTAB and Van Cittert with the paper's differential filter (whole
     call), reported as an extra key."""
     _, ubar = germano_inputs(w, torch, gd, dev)
-    r = {s: germano_result(gd, torch, ubar, w, s, max(5, args.steps // 2), args.warmup, not args.no_tune, dev)
+    r = {s: germano_result(gd, torch, ubar, w, s, max(5, args.steps // 2), args.warmup, dev)
          for s in ("bicgstab", "vc")}
     del ubar
     return {"workload": w["desc"], "solvers": r, "ms": r["bicgstab"]["ms"],

@@ -426,8 +426,12 @@ int germano_filter_apply(const gd_grid *grid, double gamma, const void *x, void 
 int deconvolve_germano(int32_t solver, const gd_grid *grid, double gamma, const void *ubar, void *u,
                        const gd_opts *opts, void *work, size_t work_bytes, gd_info *info, void *stream);
 /* As deconvolve_autotune, for deconvolve_germano with this grid and solver:
- * times the launch configurations of the solve on the Fourier coefficients
- * of ubar and remembers the fastest.  The trials run on the workspace: u
+ * times the launch configurations of the streamed solve on the Fourier
+ * coefficients of ubar and remembers the fastest.  That solve runs from
+ * GD_INIT_GIVEN and GD_INIT_WARM starts, where a grid has more groups of
+ * wavenumbers of one |k|^2 than the GPU's registers hold, and where a field does
+ * not meet tol in its storage type; other solves from GD_INIT_UBAR and
+ * GD_INIT_ZERO do not use the choice.  The trials run on the workspace: u
  * (non-NULL, as for deconvolve_germano) is not written, and ubar must not
  * overlap the workspace.  Synchronous. */
 int deconvolve_germano_autotune(int32_t solver, const gd_grid *grid, double gamma, const void *ubar, void *u,
@@ -524,7 +528,9 @@ int gd_last_launch(gd_launch_info *out);
  * buf[4k+3] = latest per-field reduction, in device wall-clock ticks
  * (hipDeviceAttributeWallClockRate kHz), for 4k + 3 < capacity.  The caller
  * initialises buf (first arrival to UINT64_MAX, the others to 0) before each
- * solve.  buf: device memory of `capacity` uint64 entries; NULL switches
+ * solve.  While set, solves take the streaming kernel, which has these
+ * barriers, also where they would be solved in registers or on groups of
+ * wavenumbers.  buf: device memory of `capacity` uint64 entries; NULL switches
  * recording off. */
 int gd_set_trace(uint64_t *buf, int64_t capacity);
 

@@ -92,11 +92,6 @@ __device__ __forceinline__ int64_t plane_shift(int64_t pz, int nz, int dz) {
     return pz - z + wrap(z + dz, nz);
 }
 
-// offsets of tap t of NT (9: 2D, 27: 3D)
-template <int NT> __device__ __forceinline__ int tap_dz(int t) { return NT == 27 ? t / 9 - 1 : 0; }
-__device__ __forceinline__ int tap_dy(int t) { return (t % 9) / 3 - 1; }
-__device__ __forceinline__ int tap_dx(int t) { return t % 3 - 1; }
-
 // ---------------------------------------------------------------- small kernels
 
 // the bf16 weights, and FP32 copies of them for the two end layers (k_conv_end's order)

@@ -400,7 +400,9 @@ __global__ __launch_bounds__(kThreads) void k_red_solve(Params P) {
 // completes a field writes its info record.  A field whose recursive residual
 // met the tolerance and whose true residual does not (the rounding of the
 // storage type) is handed to the general solver, which replaces its residual
-// and goes on.  Bound by one read of ubar_hat and one write of u_hat.
+// and goes on.  Bound by what it computes per coefficient (G_hat's FP64 division,
+// the index's divisions, 64-bit class numbers) with one load in flight: 349 us
+// for 16 x 2048^2 FP32, 1.5 TB/s of the one read and the one write.
 template <typename T>
 __global__ __launch_bounds__(kExpand) void k_expand(const T *UB, T *U, Params P) {
     typedef T V2 __attribute__((ext_vector_type(2)));

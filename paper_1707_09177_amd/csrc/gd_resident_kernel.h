@@ -19,7 +19,8 @@
 // passes, streamed -> resident: 64^2 FP64 BiCGSTAB 285 -> 47 us, 16 x 256^2
 // FP32 CG 342 -> 55, 8 x 1024^2 FP32 BiCGSTAB 1146 -> 322, 16 x 2048^2 FP32
 // BiCGSTAB 5016 -> 2915 (16 rounds) and Van Cittert 1752 -> 1171, 3 x 128^3
-// FP32 BiCGSTAB 1742 -> 403, 3 x 90 x 100 x 97 FP64 CG 769 -> 335.
+// FP32 BiCGSTAB 1742 -> 400, FP64 CG on three fields of 97 x 100 x 90 points (z, y,
+// x; 130 boxes, three rounds) 769 -> 327 and of 90 x 100 x 97 (120, two) 702 -> 223.
 //
 // Layout: a column of a box is one x and KZ consecutive points of the march
 // axis (y in 2D, z in 3D): a thread marches its columns with a three-value
@@ -41,10 +42,12 @@ namespace gdres {
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
 
-// Points per thread (KC columns of KZ points), so that a solver's vectors fit
-// the 128 registers of four waves per SIMD without spilling: with 32 points a
-// Van Cittert pass on 1024^2 took 2.4 times as long as with 16, CG with 24
-// 1.7 times as long.  BiCGSTAB's fifth vector, f0, is in LDS where a thread
+// Points per thread (KC columns of KZ points): a solver's vectors take 32 to 64
+// of the 128 registers of four waves per SIMD.  With addresses and temporaries
+// Van Cittert and steepest descent then spill up to 6 registers, CG 3 to 42 and
+// BiCGSTAB 21 to 125 (60 in two columns of 8 points, FP32), the kernels of 12 and
+// 24 points 125 to 181; columns of 4 points none.  With 32 points a Van Cittert pass on 1024^2 took 2.4 times as long as with
+// 16, CG with 24 1.7 times as long.  BiCGSTAB's fifth vector, f0, is in LDS where a thread
 // has more than kSmallZ points and the box leaves room (8 x 1024^2 FP32: 320 us
 // for 5 passes, in registers 378).  CG and, in 3D, Van Cittert and steepest
 // descent take 24 points where a field fits in no other way (160^3 FP32 CG: 249 us

@@ -184,8 +184,8 @@ def last_launch() -> dict:
 
 
 def set_trace(buf: torch.Tensor | None):
-    """Record grid-barrier timestamps of later solves into ``buf`` (int64, on
-    the device; see gd_set_trace).  ``None`` switches recording off."""
+    """Record grid-barrier timestamps of later solves, which stream then, into
+    ``buf`` (int64, on the device; see gd_set_trace).  ``None`` switches recording off."""
     if buf is None:
         load().gd_set_trace(None, 0)
     else:
@@ -443,8 +443,9 @@ class GermanoDeconvolver(Deconvolver):
         return call
 
     def autotune(self, ubar: torch.Tensor, out: torch.Tensor | None = None, stream=None) -> dict:
-        """Time the launch configurations on these buffers and keep the
-        fastest for later solves of this shape (deconvolve_germano_autotune)."""
+        """Time the launch configurations of the streamed solve on these buffers
+        and keep the fastest for later solves of this shape that stream: from
+        given and warm starts (deconvolve_germano_autotune)."""
         if tuple(ubar.shape) != self.shape or ubar.dtype != self.dtype or ubar.device != self.work.device:
             raise ValueError(f"ubar must have shape {self.shape} and dtype {self.dtype} on {self.work.device}")
         u = _out(out, self.shape, ubar)
