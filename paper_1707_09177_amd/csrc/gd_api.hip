@@ -449,6 +449,7 @@ std::string key_uniform(int solver, const gd_grid *g, bool aligned) {
 TuneCfg untuned(const gd_grid *g, bool aligned, bool spec, int ncu) {
     TuneCfg c;
     if (spec) return c;
+    c.res = kResRule;
     c.tpw = 1;
     c.tail = 0;
     if (g->ndim == 3) {

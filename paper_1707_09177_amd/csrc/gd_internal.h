@@ -185,7 +185,7 @@ struct TuneCfg {
     int wc = 0;   // per-wave tile claims
     int bpc = kBlocksPerCu;  // workgroups per CU (0: as many as fit)
     int segs = 0;  // > 0: every column is cut into this many long tiles, whatever the wave count
-    int res = kResRule;  // whether a field that fits the chip's registers is solved there (the rest does not apply then)
+    int res = kResNever;  // whether a field that fits the chip's registers is solved there (the rest does not apply then)
 };
 
 // A solve on a stored Fourier spectrum (the differential filter); hw is the
